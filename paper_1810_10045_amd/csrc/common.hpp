@@ -160,6 +160,12 @@ struct bf16_t {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// The same at the alignment of an element only: rows whose width is no
+// multiple of 16 bytes start anywhere. gfx950 loads and stores global memory
+// 16 bytes at a time at any address (unaligned access mode), so the compiler
+// emits the one instruction for these as for the aligned types.
+typedef float f32x4e __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4e __attribute__((ext_vector_type(4), aligned(2)));
 
 // Gradient rows are read exactly once: stream them past the caches.
 #ifndef LMZ_STREAM_LOADS
@@ -167,6 +173,22 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 #endif
 template <typename T>
 __device__ __forceinline__ T stream_load(const T* p) {
+#if LMZ_STREAM_LOADS
+  return __builtin_nontemporal_load(p);
+#else
+  return *p;
+#endif
+}
+
+// (of their own: a template argument drops the type's alignment)
+__device__ __forceinline__ f32x4 stream_load_e(const f32x4e* p) {
+#if LMZ_STREAM_LOADS
+  return __builtin_nontemporal_load(p);
+#else
+  return *p;
+#endif
+}
+__device__ __forceinline__ u32x4 stream_load_e(const u32x4e* p) {
 #if LMZ_STREAM_LOADS
   return __builtin_nontemporal_load(p);
 #else
@@ -185,7 +207,7 @@ template <>
 struct RowVec<float, 4> {
   using raw_t = f32x4;
   static __device__ __forceinline__ raw_t load(const float* p) {
-    return stream_load(reinterpret_cast<const f32x4*>(p));
+    return stream_load_e(reinterpret_cast<const f32x4e*>(p));
   }
   static __device__ __forceinline__ void add(float* acc, const raw_t& r) {
     acc[0] += r.x; acc[1] += r.y; acc[2] += r.z; acc[3] += r.w;
@@ -203,7 +225,7 @@ template <>
 struct RowVec<bf16_t, 8> {
   using raw_t = u32x4;
   static __device__ __forceinline__ raw_t load(const bf16_t* p) {
-    return stream_load(reinterpret_cast<const u32x4*>(p));
+    return stream_load_e(reinterpret_cast<const u32x4e*>(p));
   }
   static __device__ __forceinline__ void add(float* acc, const raw_t& r) {
     const uint32_t w[4] = {r.x, r.y, r.z, r.w};
@@ -226,13 +248,14 @@ struct RowVec<bf16_t, 1> {
   }
 };
 
-// Store VEC fp32 values (16-byte stores when VEC is a multiple of 4).
+// Store VEC fp32 values (16-byte stores when VEC is a multiple of 4), at the
+// alignment of a float.
 template <int VEC>
 __device__ __forceinline__ void store_vec(float* p, const float* v) {
   if constexpr (VEC % 4 == 0) {
 #pragma unroll
     for (int i = 0; i < VEC; i += 4)
-      *reinterpret_cast<float4*>(p + i) = make_float4(v[i], v[i + 1], v[i + 2], v[i + 3]);
+      *reinterpret_cast<f32x4e*>(p + i) = f32x4e{v[i], v[i + 1], v[i + 2], v[i + 3]};
   } else {
 #pragma unroll
     for (int i = 0; i < VEC; ++i) p[i] = v[i];
@@ -337,7 +360,7 @@ __device__ __forceinline__ void load_vec(const float* p, float* v) {
   if constexpr (VEC % 4 == 0) {
 #pragma unroll
     for (int i = 0; i < VEC; i += 4) {
-      float4 t = *reinterpret_cast<const float4*>(p + i);
+      const f32x4e t = *reinterpret_cast<const f32x4e*>(p + i);
       v[i] = t.x; v[i + 1] = t.y; v[i + 2] = t.z; v[i + 3] = t.w;
     }
   } else {

@@ -1,0 +1,90 @@
+"""Seg-Sum over rows whose width or start is no multiple of a 16-byte vector:
+the last lane's vector repeats columns of the lane before it, partial rows are
+exchanged column by column, and a last column tile narrower than a vector
+starts one vector earlier."""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import gpu_helpers as H  # noqa: E402
+import oracle  # noqa: E402
+from paper_1810_10045_amd import synth  # noqa: E402
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.fixture(scope="module")
+def lz():
+    from paper_1810_10045_amd import lmzipf
+    return lmzipf
+
+
+# Widths around one vector (4 fp32, 8 bf16 columns), around a fix-up tile (256)
+# and a walk tile (1024) with less than a vector in the last one (1025..1027
+# fp32, ..1031 bf16), past the one-launch form (4097), and the first column.
+WIDTHS = [("f32", D, o) for D, o in ((3, 0), (4, 1), (5, 0), (7, 0), (255, 0), (257, 1), (650, 0),
+                                     (1022, 1), (1024, 3), (1025, 0), (1027, 0), (2049, 0),
+                                     (4097, 0))] + \
+         [("bf16", D, o) for D, o in ((7, 0), (8, 1), (9, 0), (300, 0), (517, 1), (1023, 0),
+                                      (1028, 0), (1031, 0), (2048, 4), (4095, 0))]
+
+
+@pytest.mark.parametrize("gdt,D,first", WIDTHS, ids=[f"{g}-D{d}+{o}" for g, d, o in WIDTHS])
+def test_segsum_any_width(lz, gdt, D, first):
+    """The sums against the oracle (rows of one token exact); into table rows,
+    and with SGD and Adam, bit for bit what lm_segsum and then the call of its
+    own give; columns outside the table's D untouched."""
+    K, V = 5000, 700
+    print(f"segsum {gdt} D={D} first column {first}", flush=True)
+    ids = synth.zipf_ids_permuted(K, V, 1.1, 300 + D, 5, np.int32)
+    wide = torch.from_numpy(synth.normal_rows(K, D + 5, 301 + D)).to(DEV)
+    wide = wide.to(torch.bfloat16) if gdt == "bf16" else wide
+    grad = wide[:, first:first + D]
+    r = lz.unique(torch.from_numpy(ids).to(DEV), V)
+    seg = (grad, r.perm, r.inverse, r.offsets, r.num_unique)
+    sums = lz.segsum(*seg, dev_err=r.dev_err)
+    base = torch.from_numpy(synth.normal_rows(V, D + 5, 302 + D, 0.02)).to(DEV)
+
+    def table():
+        t = base.clone()
+        return t, t[:, first:first + D]
+
+    whole = {}
+    for how in ("rows", "sgd", "adam"):
+        t1, a = table()
+        t2, b = table()
+        if how == "rows":
+            lz.segsum_rows(*seg, r.uniq, a, dev_err=r.dev_err)
+            lz.fill_values(sums, r.uniq, r.num_unique, b, mode="scatter", dev_err=r.dev_err)
+        elif how == "sgd":
+            lz.segsum_sgd(*seg, r.uniq, a, 0.1, dev_err=r.dev_err)
+            lz.sparse_apply(b, r.uniq, r.num_unique, sums, "sgd", lr=0.1, dev_err=r.dev_err)
+        else:
+            m1, v1 = table()[1].abs(), table()[1].square()
+            m1, v1 = (torch.empty_like(t1)[:, first:first + D].copy_(x) for x in (m1, v1))
+            m2, v2 = (torch.empty_like(t1)[:, first:first + D].copy_(x) for x in (m1, v1))
+            lz.segsum_adam(*seg, r.uniq, a, m1, v1, step=3, dev_err=r.dev_err)
+            lz.sparse_apply(b, r.uniq, r.num_unique, sums, "adam", lr=1e-3, step=3, m=m2, v=v2,
+                            dev_err=r.dev_err)
+            assert torch.equal(m1, m2) and torch.equal(v1, v2), "moments differ"
+        assert torch.equal(t1, t2), f"{how}: not lm_segsum and then the call of its own"
+        outside = torch.ones(D + 5, dtype=torch.bool)
+        outside[first:first + D] = False
+        assert torch.equal(t1[:, outside], base[:, outside]), f"{how}: wrote outside its columns"
+        whole[how] = t1
+    torch.cuda.synchronize()
+    lz.check(r.dev_err)
+    o = H.assert_unique_matches(r, ids, V, oracle)
+    U = len(o[0])
+    host = (np.ascontiguousarray(grad.contiguous().view(torch.int16).cpu().numpy().view(np.uint16))
+            if gdt == "bf16" else np.ascontiguousarray(grad.cpu().numpy()))
+    ref = oracle.segsum(host, o[3], U)
+    got = sums[:U].double().cpu().numpy()
+    H.check_rows(got, ref, H.sum_of_squares(host, o[3], U, oracle), gdt)
+    H.assert_single_rows_exact(got, ref, o[1])
