@@ -48,11 +48,13 @@
 // lm_segsum_sgd and lm_segsum_adam (the update instantiations, OP) update
 // those rows instead of writing them, the sum in the same order and the
 // update the same arithmetic as lm_sparse_apply's (sgd_value, adam_value).
-// The walk then closes a gather batch after its kEnds-th segment end and
-// loads the table rows of those ends (Adam: the parameters, m and v) with
-// its gradient rows, through buffer resources whose range is empty where no
-// row is needed (such a load reads nothing and returns zeros), so an update
-// costs no round trip of its own.
+// The walk loads the table row (Adam: those of the parameters, m and v) when
+// the segment has ended; where SGD finds many short segments (the EARLY
+// instantiations, see may_be_early) it closes a gather batch after its
+// kEnds-th segment end and loads the table rows of those ends with its
+// gradient rows, through buffer resources whose range is empty where no row
+// is needed (such a load reads nothing and returns zeros), so an update costs
+// no round trip of its own.
 #pragma once
 
 #include <atomic>
@@ -87,8 +89,7 @@ namespace lmz {
 #define LMZ_SEG_SGD_RF4 3            // lm_segsum_sgd: rows per batch with 4 vectors per lane,
 #endif                               // chunks below LMZ_SEG_LONG_R (others as lm_segsum)
 #ifndef LMZ_SEG_ADAM_RF4
-#define LMZ_SEG_ADAM_RF4 2           // lm_segsum_adam: the same, every chunk length (one end,
-                                     // three table rows per batch; 4 at most with fewer vectors)
+#define LMZ_SEG_ADAM_RF4 4           // lm_segsum_adam: most rows per batch with 4 vectors per lane
 #endif
 #ifndef LMZ_SEG_FIX_RF
 #define LMZ_SEG_FIX_RF 16            // partial rows per wave in flight in the fix-up
@@ -437,7 +438,7 @@ __device__ __forceinline__ void fused_fix(const SegArgs& a) {
 }
 
 template <typename GT, int VEC, int NV, int RF, int R, int T, int NTHR, bool FUSED, int OP,
-          bool TAIL>
+          bool TAIL, bool EARLY>
 __global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
   if constexpr (FUSED) {
     if (static_cast<int>(blockIdx.x) >= a.main_blocks) {
@@ -624,13 +625,40 @@ __global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
       store_vec<VEC>(row + col_ld[v], acc[v]);
     }
   };
+  // An update not EARLY: the table row at dst (and Adam's moments) updated with acc; every
+  // vector is loaded before the first store (lanes may share columns).
+  auto update_row = [&](float* dst) {
+    if (!dst) return;
+    const int64_t off = dst - a.out;
+    float p[NV][VEC], m[NV][VEC], s[NV][VEC];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      load_vec<VEC>(dst + col_ld[v], p[v]);
+      if constexpr (OP == kOpAdam) {
+        load_vec<VEC>(a.m + off + col_ld[v], m[v]);
+        load_vec<VEC>(a.v + off + col_ld[v], s[v]);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        if constexpr (OP == kOpAdam) adam_value(p[v][e], m[v][e], s[v][e], acc[v][e], a.opt);
+        else sgd_value(p[v][e], acc[v][e], a.opt);
+      }
+      if (!col_ok[v]) continue;
+      store_vec<VEC>(dst + col_ld[v], p[v]);
+      if constexpr (OP == kOpAdam) {
+        store_vec<VEC>(a.m + off + col_ld[v], m[v]);
+        store_vec<VEC>(a.v + off + col_ld[v], s[v]);
+      }
+    }
+  };
   const GT* __restrict__ grad = static_cast<const GT*>(a.grad);
   bool bad_row = false;
-  // Update instantiations: segment ends per batch, and table rows per end
-  // (Adam: the parameters, m and v; one end per batch, as three rows per
-  // end fill the registers).
-  constexpr int kEnds = OP == kOpSgd ? LMZ_SEG_SGD_ENDS : 1;
-  constexpr int kRows = OP == kOpAdam ? 3 : 1;
+  // EARLY: segment ends, and so table rows, per batch.
+  constexpr int kEnds = EARLY ? LMZ_SEG_SGD_ENDS : 1;
   static_assert(kEnds >= 1 && kEnds <= RF, "table rows per batch");
 
 #pragma unroll
@@ -640,11 +668,11 @@ __global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
     const int hi = q_end - wbase < kWave ? q_end - wbase : kWave;
     for (int j0 = lo; j0 < hi;) {
       int n = hi - j0 < RF ? hi - j0 : RF;
-      // Updates: at most kEnds segment ends per batch (bm: their bits),
-      // whose table rows load with the batch's gradient rows.
+      // EARLY: at most kEnds segment ends per batch (bm: their bits), whose
+      // table rows load with the batch's gradient rows.
       uint64_t bm = 0;
-      float tb[kEnds][kRows][NV][VEC];
-      if constexpr (OP != kOpStore) {
+      float tb[kEnds][NV][VEC];
+      if constexpr (EARLY) {
         bm = (ends[w] >> j0) & ((uint64_t(1) << n) - 1);
         uint64_t past = bm;  // the ends after the first kEnds
 #pragma unroll
@@ -663,12 +691,9 @@ __global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
             const int s = read_lane(sw[w], j);
             if (!(s == s_f && started_before) && s >= 0 && s < a.u_cap) orow = read_lane(orw[w], j);
           }
+          const __amdgpu_buffer_rsrc_t rs = table_row(a, a.out, orow);
 #pragma unroll
-          for (int x = 0; x < kRows; ++x) {
-            const __amdgpu_buffer_rsrc_t rs = table_row(a, x == 0 ? a.out : x == 1 ? a.m : a.v, orow);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) table_vec<VEC>(rs, col_ld[v], tb[k][x][v]);
-          }
+          for (int v = 0; v < NV; ++v) table_vec<VEC>(rs, col_ld[v], tb[k][v]);
         }
       }
       // Always RF row loads (rows past n repeat row n-1, a cache hit): a load
@@ -704,38 +729,24 @@ __global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
               bad_row |= rows && orow < 0 && s >= 0 && s < a.u_cap;
               dst = (s >= 0 && s < a.u_cap && orow >= 0) ? a.out + orow * a.ld_out : nullptr;
             }
-            if constexpr (OP == kOpSgd) {
+            if constexpr (EARLY) {
               if (!part) {  // the batch's k-th end: table row k
                 const int k = __popcll(bm & ((uint64_t(1) << (j - j0)) - 1));
 #pragma unroll
                 for (int v = 0; v < NV; ++v)
 #pragma unroll
                   for (int e = 0; e < VEC; ++e) {
-                    float t = tb[0][0][v][e];
+                    float t = tb[0][v][e];
 #pragma unroll
-                    for (int x = 1; x < kEnds; ++x) t = k == x ? tb[x][0][v][e] : t;
+                    for (int x = 1; x < kEnds; ++x) t = k == x ? tb[x][v][e] : t;
                     sgd_value(t, acc[v][e], a.opt);
                     acc[v][e] = t;
                   }
               }
-            } else if constexpr (OP == kOpAdam) {
-              if (!part) {  // the batch's one end: the parameters into acc, the moments in place
-#pragma unroll
-                for (int v = 0; v < NV; ++v)
-#pragma unroll
-                  for (int e = 0; e < VEC; ++e) {
-                    adam_value(tb[0][0][v][e], tb[0][1][v][e], tb[0][2][v][e], acc[v][e], a.opt);
-                    acc[v][e] = tb[0][0][v][e];
-                  }
-                if (dst) {
-                  const int64_t off = dst - a.out;
-#pragma unroll
-                  for (int v = 0; v < NV; ++v) {
-                    if (!col_ok[v]) continue;
-                    store_vec<VEC>(a.m + off + col_ld[v], tb[0][1][v]);
-                    store_vec<VEC>(a.v + off + col_ld[v], tb[0][2][v]);
-                  }
-                }
+            } else if constexpr (OP != kOpStore) {
+              if (!part) {
+                update_row(dst);
+                dst = nullptr;
               }
             }
             if (dst) {
@@ -913,11 +924,12 @@ constexpr int rf_sgd_for() {
   return NV >= 4 && R < LMZ_SEG_LONG_R ? LMZ_SEG_SGD_RF4 : rf_for<NV, R>();
 }
 
-// lm_segsum_adam's rows per batch: three table rows per end take registers
-// from the gradient batch, at every chunk length.
+// lm_segsum_adam's rows per batch: as lm_segsum's, but for its three table
+// rows at most 4 rows of 4 vectors, or 8 of fewer.
 template <int NV, int R>
 constexpr int rf_adam_for() {
-  return NV >= 4 ? LMZ_SEG_ADAM_RF4 : (rf_for<NV, R>() < 4 ? rf_for<NV, R>() : 4);
+  constexpr int rf = rf_for<NV, R>(), most = NV >= 4 ? LMZ_SEG_ADAM_RF4 : 8;
+  return rf > most ? most : rf;
 }
 
 // Workgroups of the plain walk (kOpStore) that fit on a compute unit, fused or
@@ -926,10 +938,11 @@ constexpr int rf_adam_for() {
 template <typename GT, int VEC, int NV, int R, bool TAIL>
 int plain_blocks(bool fused);
 
-template <typename GT, int VEC, int NV, int R, int OP, bool TAIL>
+template <typename GT, int VEC, int NV, int R, int OP, bool TAIL, bool EARLY>
 static void launch_one(SegArgs& a, int tiles, hipStream_t st) {
-  constexpr int RFp = rf_for<NV, R>(), T = t_for<R>();
-  constexpr int RF = OP == kOpSgd ? rf_sgd_for<NV, R>() : OP == kOpAdam ? rf_adam_for<NV, R>() : RFp;
+  constexpr int T = t_for<R>();
+  constexpr int RF = EARLY ? rf_sgd_for<NV, R>()
+                     : OP == kOpAdam ? rf_adam_for<NV, R>() : rf_for<NV, R>();
   constexpr int CT = NV * kWave * VEC;
   a.tiles = tiles;
   a.tile_cols = CT;
@@ -951,14 +964,50 @@ static void launch_one(SegArgs& a, int tiles, hipStream_t st) {
     if (fused) {
       a.main_blocks = (a.nchunks + kFusedWaves - 1) / kFusedWaves * tiles;
       const int fix_blocks = (a.nchunks + kFusedSpan - 1) / kFusedSpan * a.fix_tiles;
-      k_segsum<GT, VEC, NV, RF, R, T, kFusedThreads, true, OP, TAIL>
+      k_segsum<GT, VEC, NV, RF, R, T, kFusedThreads, true, OP, TAIL, EARLY>
           <<<dim3(a.main_blocks + fix_blocks), kFusedThreads, 0, st>>>(a);
       return;
     }
   }
   const dim3 grid((a.nchunks + kSegWaves - 1) / kSegWaves, tiles);
-  k_segsum<GT, VEC, NV, RF, R, T, kSegThreads, false, OP, TAIL>
+  k_segsum<GT, VEC, NV, RF, R, T, kSegThreads, false, OP, TAIL, EARLY>
       <<<grid, kSegThreads, LMZ_SEG_LDS_PAD, st>>>(a);
+}
+
+// Whether an update loads the table rows of a batch's segment ends with the
+// batch's gradient rows (early). An end then costs no round trip of its own,
+// but a batch closes at its second end and has room for fewer gradient rows.
+// Otherwise (late) the walk keeps lm_segsum's batches, waits for the table row
+// at every end, and needs fewer registers (more waves hide the waits).
+// Measured, early / late, us per call:
+//   SGD fp32, D = 1024: 65,536 ids over 800K words 86.9 / 94.0, 200,000 over
+//     100K 288 / 315, over 12,500 (K / V = 16) 208 / 216, over 6,250 (32) 203 /
+//     195, over 781 176 / 151; D = 512: 600,000 over 300K (chunks of 512)
+//     469 / 412;
+//   SGD bf16, D = 1024: 100,000 ids over 100K words 93.4 / 84.8;
+//   Adam (one end, 2 rows per batch early), the same tables: 262,144 ids over
+//     2M words 954 / 909, 65,536 over 800K 226 / 210, 200,000 over 400K 646 /
+//     494, D = 1792: 19,200 over 98 67 / 39. Late with 2 or 3 rows per batch,
+//     or loading the three rows' vectors one or two at a time, measured within
+//     2% of 4 rows and all vectors at the large sizes and 1-10% slower at
+//     19,200 ids.
+// So only SGD with fp32 rows, chunks below 512 rows and no more than 32
+// tokens per type it may find (there are at most min(K, rows_cap)) is early.
+template <typename GT, int OP, int R>
+constexpr bool may_be_early() {
+  return OP == kOpSgd && sizeof(GT) == 4 && R < LMZ_SEG_LONG_R;
+}
+constexpr int kEarlyTokensPerType = 32;
+
+template <typename GT, int VEC, int NV, int R, int OP, bool TAIL>
+static void launch_when(SegArgs& a, int tiles, hipStream_t st) {
+  if constexpr (may_be_early<GT, OP, R>()) {
+    if (a.K < kEarlyTokensPerType * a.u_cap) {
+      launch_one<GT, VEC, NV, R, OP, TAIL, true>(a, tiles, st);
+      return;
+    }
+  }
+  launch_one<GT, VEC, NV, R, OP, TAIL, false>(a, tiles, st);
 }
 
 template <typename GT, int VEC, int NV, int OP, bool TAIL>
@@ -966,12 +1015,12 @@ static hipError_t launch_r(SegArgs& a, hipStream_t st) {
   constexpr int CT = NV * kWave * VEC;
   const int tiles = (a.D + CT - 1) / CT;
   switch (a.R) {
-    case 16: launch_one<GT, VEC, NV, 16, OP, TAIL>(a, tiles, st); break;
-    case 32: launch_one<GT, VEC, NV, 32, OP, TAIL>(a, tiles, st); break;
-    case 64: launch_one<GT, VEC, NV, 64, OP, TAIL>(a, tiles, st); break;
-    case 128: launch_one<GT, VEC, NV, 128, OP, TAIL>(a, tiles, st); break;
-    case 256: launch_one<GT, VEC, NV, 256, OP, TAIL>(a, tiles, st); break;
-    default: launch_one<GT, VEC, NV, 512, OP, TAIL>(a, tiles, st); break;
+    case 16: launch_when<GT, VEC, NV, 16, OP, TAIL>(a, tiles, st); break;
+    case 32: launch_when<GT, VEC, NV, 32, OP, TAIL>(a, tiles, st); break;
+    case 64: launch_when<GT, VEC, NV, 64, OP, TAIL>(a, tiles, st); break;
+    case 128: launch_when<GT, VEC, NV, 128, OP, TAIL>(a, tiles, st); break;
+    case 256: launch_when<GT, VEC, NV, 256, OP, TAIL>(a, tiles, st); break;
+    default: launch_when<GT, VEC, NV, 512, OP, TAIL>(a, tiles, st); break;
   }
   return hipGetLastError();
 }

@@ -15,14 +15,14 @@ int plain_blocks(bool fused) {
     hipError_t e;
     if constexpr (VEC >= 2) {
       e = fused ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                      &b, k_segsum<GT, VEC, NV, RF, R, T, kFusedThreads, true, kOpStore, TAIL>,
+                      &b, k_segsum<GT, VEC, NV, RF, R, T, kFusedThreads, true, kOpStore, TAIL, false>,
                       kFusedThreads, 0)
                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                      &b, k_segsum<GT, VEC, NV, RF, R, T, kSegThreads, false, kOpStore, TAIL>,
+                      &b, k_segsum<GT, VEC, NV, RF, R, T, kSegThreads, false, kOpStore, TAIL, false>,
                       kSegThreads, LMZ_SEG_LDS_PAD);
     } else {
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &b, k_segsum<GT, VEC, NV, RF, R, T, kSegThreads, false, kOpStore, TAIL>, kSegThreads,
+          &b, k_segsum<GT, VEC, NV, RF, R, T, kSegThreads, false, kOpStore, TAIL, false>, kSegThreads,
           LMZ_SEG_LDS_PAD);
     }
     if (e != hipSuccess) {

@@ -88,3 +88,31 @@ def test_segsum_any_width(lz, gdt, D, first):
     got = sums[:U].double().cpu().numpy()
     H.check_rows(got, ref, H.sum_of_squares(host, o[3], U, oracle), gdt)
     H.assert_single_rows_exact(got, ref, o[1])
+
+
+@pytest.mark.parametrize("K,V,D,gdt", [(6400, 199, 1024, "f32"), (6400, 200, 512, "f32"),
+                                       (6400, 201, 650, "f32"), (300_000, 200_000, 64, "f32"),
+                                       (9000, 8000, 520, "bf16"), (5000, 1, 300, "f32")])
+def test_updates_on_either_side_of_the_early_rule(lz, K, V, D, gdt):
+    """SGD's table rows load with the gradient rows below 32 tokens per type
+    (fp32, chunks below 512 rows), else, and for Adam, after each segment: the
+    tables are those of lm_segsum and then lm_sparse_apply, bit for bit."""
+    print(f"update K={K} V={V} D={D} {gdt}", flush=True)
+    ids = torch.from_numpy(synth.zipf_ids(K, V, 1.0, 400 + K, np.int64)).to(DEV)
+    grad = torch.from_numpy(synth.normal_rows(K, D, 401 + K)).to(DEV)
+    grad = grad.to(torch.bfloat16) if gdt == "bf16" else grad
+    r = lz.unique(ids, V)
+    seg = (grad, r.perm, r.inverse, r.offsets, r.num_unique)
+    sums = lz.segsum(*seg, dev_err=r.dev_err)
+    p = torch.from_numpy(synth.normal_rows(V, D, 402, 0.02)).to(DEV)
+    m, v = p.clone(), p.square()
+    a, b = p.clone(), p.clone()
+    lz.segsum_sgd(*seg, r.uniq, a, 0.1, dev_err=r.dev_err)
+    lz.sparse_apply(b, r.uniq, r.num_unique, sums, "sgd", lr=0.1, dev_err=r.dev_err)
+    assert torch.equal(a, b)
+    t1, t2 = ([x.clone() for x in (p, m, v)] for _ in range(2))
+    lz.segsum_adam(*seg, r.uniq, *t1, step=2, weight_decay=0.01, dev_err=r.dev_err)
+    lz.sparse_apply(t2[0], r.uniq, r.num_unique, sums, "adam", lr=1e-3, step=2, weight_decay=0.01,
+                    m=t2[1], v=t2[2], dev_err=r.dev_err)
+    assert all(torch.equal(x, y) for x, y in zip(t1, t2))
+    lz.check(r.dev_err)
