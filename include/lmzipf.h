@@ -23,7 +23,7 @@
  *   torch CUDA tensor); host pointers are never accepted for those.
  * - The caller owns every buffer. The library allocates nothing and keeps
  *   no pointer past the call. Its only global state is a per-process call
- *   counter (lm_segsum's flag tags) and the lm_segsum_set_two_launches
+ *   counter (lm_segsum's tags) and the lm_segsum_set_two_launches
  *   setting. All work is enqueued on `stream` (a hipStream_t; NULL is the
  *   default stream) and the call returns without synchronising.
  * - Counts that the GPU computes (num_unique, n_src, ...) stay on the device.
@@ -152,8 +152,8 @@ int lm_unique_noalloc(const void* ids, int32_t idtype, int64_t K, int64_t V,
  * one row of E, so the reverse map is an accumulation):
  *     out[u, :] = sum over i in [offsets[u], offsets[u+1]) of grad[perm[i], :]
  * for u < U = *num_unique, accumulated in fp32 in a fixed order, so repeated
- * calls give bit-identical results. The order depends on K, D, u_cap (the
- * walk's chunks are sized from min(K, u_cap)), the launch form and the
+ * calls give bit-identical results. The order depends on K, D, u_cap and
+ * U (the walk's chunks are sized from them), the launch form and the
  * number of compute units `stream` may use (the chunks are also sized to
  * fill whole rounds of the waves that fit there: all of the device's, or
  * those of a stream created with hipExtStreamCreateWithCUMask), not on the
@@ -174,11 +174,13 @@ int lm_unique_noalloc(const void* ids, int32_t idtype, int64_t K, int64_t V,
  *            256-byte aligned; no initial contents are required.
  *
  * With D <= 4096 and rows of at least 16 bytes, the segments that span the
- * walk's chunks are summed by workgroups of the same launch, which wait for
- * per-chunk flags tagged with a per-call value from a process-wide counter
+ * walk's chunks are summed in the same launch, by the wave that finishes their
+ * last piece or, the longest ones, by workgroups that wait for the pieces
  * (bounded waits; LM_DEVERR_SPIN if one gave up, which a correct call never
- * does). Otherwise, always while `stream` is being captured into a graph (a
- * replay would repeat the tag), and while lm_segsum_set_two_launches is on,
+ * does). Pieces are announced in words tagged with a per-call value from a
+ * process-wide counter. Otherwise, always while `stream` is being captured
+ * into a graph (a replay would repeat the tag), and while
+ * lm_segsum_set_two_launches is on,
  * they are summed by a second launch.
  * ------------------------------------------------------------------------ */
 size_t lm_segsum_workspace_bytes(int64_t K, int64_t D);

@@ -114,19 +114,39 @@ int stream_cus(hipStream_t st) {
 // Measured at K = 1,048,576, D = 2048 fp32 (two column tiles, room for
 // 2,048 waves): 2,088 chunks (4,176 waves) 1,591 us, 3,072 chunks 1,488 us.
 // Where the last round was half full or more (the bf16 merge: 10,347 waves
-// on room for 4,096) rounding up changed nothing measurable, and inputs of
-// less than one round are left as they are (more chunks made the 2M
-// vocabulary 2% slower).
-int whole_rounds(int nchunks, int tiles, int64_t waves_per_round, int max_chunks) {
-  if (waves_per_round <= 0 || tiles <= 0) return nchunks;
-  const int64_t waves = int64_t(nchunks) * tiles;
+// on room for 4,096) rounding up changed nothing measurable.
+// Less than one round is filled up too where chunks are long (R >= 256): a
+// wave waits for each batch of its rows, so half as many waves leave the memory
+// half idle. Measured, fp32: 524,288 ids over 20K words, D = 512 (1,063 waves
+// on room for 2,048) 286 -> 208 us, 200,000 over 20K, D = 256 60 -> 52 us,
+// 262,144 over 2M, D = 1024 (2,048 on 4,096) 339 -> 336 us.
+// Shorter chunks (R = 32 .. 128) make kWaves waves, two workgroups on each
+// compute unit, where there would be well below that many, and no more than
+// kEnoughWaves unless a chunk would exceed R, as every cut may cost a partial
+// row. Measured, waves before -> now: Adam, D = 1792, 19,200 ids over 98 43.2
+// us (1,208) -> 39.7 (1,536 waves 41.6, 2,560 43.8); D = 300, 40,000 over 2,000
+// 40.4 (627) -> 25.2; SGD, D = 512, 106,496 over 800K 71.7 (1,664) -> 67.5;
+// bf16, D = 1792, 19,200 over 15,437 38.0 (5,058) -> 33.6 (2,560). Close to
+// kWaves it loses: 30,011 over 50K, D = 650 38.3 (1,876) -> 40.5.
+constexpr int kWaves = 2048, kFewWaves = kWaves - kWaves / 8, kEnoughWaves = 2560;
+void whole_rounds(SegArgs& a, int64_t waves_per_round) {
+  a.enough = a.nchunks;
+  if (waves_per_round <= 0 || a.tiles <= 0) return;
+  const int64_t waves = int64_t(a.nchunks) * a.tiles;
   const int64_t last = waves % waves_per_round;
-  if (waves <= waves_per_round || last == 0 || 2 * last >= waves_per_round) return nchunks;
-  const int64_t rounds = (waves + waves_per_round - 1) / waves_per_round;
-  int64_t n = (rounds * waves_per_round + tiles - 1) / tiles;
-  if (n > max_chunks) n = max_chunks;
-  return static_cast<int>(n < nchunks ? nchunks : n);
+  int64_t want = a.nchunks;
+  if (a.R >= 256 ? last != 0 && (waves < waves_per_round || 2 * last < waves_per_round)
+                 : waves > waves_per_round && last != 0 && 2 * last < waves_per_round) {
+    const int64_t rounds = (waves + waves_per_round - 1) / waves_per_round;
+    want = (rounds * waves_per_round + a.tiles - 1) / a.tiles;
+  } else if (a.R > kMinR && a.R < 256 && waves < kFewWaves) {
+    want = (kWaves + a.tiles - 1) / a.tiles;
+  }
+  if (want > a.max_chunks) want = a.max_chunks;
+  if (want > a.nchunks) a.nchunks = static_cast<int>(want);
+  a.enough = a.R < 256 ? (kEnoughWaves + a.tiles - 1) / a.tiles : a.nchunks;
 }
+
 template <int OP>
 static hipError_t run_op(SegArgs& a, int gtype, hipStream_t st) {
   const hipError_t e =
@@ -217,8 +237,8 @@ int segsum_run(const void* grad, int gtype, int64_t K, int64_t D, int64_t ld_gra
   // workgroups running in the walk's last round.
   a.fused = LMZ_SEG_FUSED != 0 && D >= (gtype == LM_F32 ? 4 : 8) && D <= LMZ_SEG_FUSED_MAX_D &&
             !two_launches();
-  // A captured launch would replay with this call's epoch every time, and a
-  // replay could take the previous replay's flags for its own: under stream
+  // A captured launch would replay with this call's tag every time, and a
+  // replay could take the previous replay's pieces for its own: under stream
   // capture the fix-up is a second launch, which keeps no state across calls.
   if (a.fused) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -228,11 +248,11 @@ int segsum_run(const void* grad, int gtype, int64_t K, int64_t D, int64_t ld_gra
     }
   }
   if (a.fused) {
-    static std::atomic<uint64_t> epoch{0x9e3779b97f4a7c15ull};
+    static std::atomic<uint64_t> calls{0x3779b97f4a7ull};  // any start
     a.flags = reinterpret_cast<uint64_t*>(w + L.flags);
-    a.epoch = epoch.fetch_add(1, std::memory_order_relaxed) + 1;
+    a.tag = calls.fetch_add(1, std::memory_order_relaxed) & ((uint64_t(1) << 44) - 1);
     const bool fail = g_force_wait_failure.load(std::memory_order_relaxed);
-    a.wait_epoch = fail ? a.epoch ^ (uint64_t(1) << 63) : a.epoch;
+    a.wait_tag = fail ? ~a.tag : a.tag;
     a.spin_limit = fail ? g_forced_spin_limit.load(std::memory_order_relaxed) : kSpinLimit;
     a.fix_tiles = static_cast<int>((D + kFusedCols - 1) / kFusedCols);
   }

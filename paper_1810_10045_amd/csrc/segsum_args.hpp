@@ -25,16 +25,17 @@ struct SegArgs {
   float* part_start;
   int32_t* desc;
   int32_t* npieces;
-  uint64_t* flags;   // fused launch: flags[c * tiles + t] == epoch once column tile t of
-  uint64_t epoch;    // chunk c (and, for t = 0, its descriptor) is visible everywhere
-  uint64_t wait_epoch;  // the value the fix-up waits for: epoch (or, with the
-                        // failure-path test hook, one no walk writes)
+  uint64_t* flags;   // fused launch: flags[c * tiles + t], the word of chunk c's tile t
+  uint64_t tag;      // marks the words of this call
+  uint64_t wait_tag;  // the tag the fix-up waits for (with the failure-path test
+                      // hook, one no walk writes)
   uint32_t spin_limit;  // polls of a flag before the wait gives up
   int main_blocks, fix_tiles, fused;
   int tiles, tile_cols;    // column tiles of the walk and the columns of one
   int thin;                // TAIL kernels: columns by which the last tile starts earlier
   int R, nchunks, rw, ww;  // cost of a position / of a segment end
   int max_chunks;          // chunks the workspace holds
+  int enough;              // chunks below nchunks that still fill the device
   const void* row_ids;     // lm_segsum_rows: type u goes to out row row_ids[u]
   int row_ids64;           //   (int64 ids when nonzero), < out_rows; nullptr: row u
   int64_t out_rows;
@@ -56,9 +57,9 @@ hipError_t seg_walk(SegArgs& a, hipStream_t st);
 template <int OP>
 void seg_fix(const SegArgs& a, hipStream_t st);
 
-// Compute units a launch on `st` may use, and the chunk count that fills
-// whole rounds of waves (segsum.hip).
+// Compute units a launch on `st` may use, and the chunk counts for the waves
+// that fit on them at once (segsum.hip).
 int stream_cus(hipStream_t st);
-int whole_rounds(int nchunks, int tiles, int64_t waves_per_round, int max_chunks);
+void whole_rounds(SegArgs& a, int64_t waves_per_round);
 
 }  // namespace lmz

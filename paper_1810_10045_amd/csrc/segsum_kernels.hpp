@@ -10,29 +10,24 @@
 //   Q = ceil((rw * K + ww * U) / N). Reads and writes thus balance across
 //   waves wherever the heads and the tail of the Zipf law fall in the sorted
 //   order (equal-length chunks left the waves of the tail, one write per row,
-//   twice as long as those of the heads). A wave finds its bounds with a
-//   32-ary search of offsets, two targets at once. The search ends at the
-//   segments holding the two bounds, which tells the wave where the first
-//   and last segment of its chunk begin and end. The segment (type) of a
-//   position is inverse[perm[i]], so a wave learns every other segment
-//   boundary of its chunk from two gathers and a ballot, without searching.
+//   twice as long as those of the heads). The waves of a workgroup find their
+//   bounds together (load_window), and every segment end of their chunks from
+//   the offsets that leaves in LDS.
 //   A segment shorter than T rows belongs entirely to the chunk holding its
 //   first position, even where it runs past the chunk end; a longer one is
 //   cut at chunk boundaries and every chunk sums its piece into a partial
 //   row:
 //     part_start[c]  the piece of a long segment that starts in chunk c and
-//                    continues past it (desc[c] names that segment),
+//                    continues past it,
 //     part_cont[c]   the piece of a long segment that started before chunk c.
-//   The chunk that starts such a segment also records in npieces[c] how many
-//   chunks after c it reaches (the chunk of its last position, from the same
-//   cost formula), so that k_segsum_fix finds every piece from one load. It
-//   sums part_start[c] and part_cont[c + 1 .. c + npieces[c]] in order: one
-//   wave per column tile for a segment of fewer than 16 further pieces, all
-//   waves of a workgroup (fixed stride split of the pieces, fixed-order
-//   combine in LDS) for a head. On the 16-byte vector path (rows of up to
-//   LMZ_SEG_FUSED_MAX_D columns) the same fix-up runs as workgroups of the
-//   walk's own launch, each waiting for the flags of the chunks and column
-//   tiles it reads (the fused launch below).
+//   Its pieces are part_start[c] and part_cont[c + 1 .. c + P], c + P being
+//   the chunk of its last position (from the same cost formula), added in a
+//   fixed order: one after the other for a segment of fewer than 16 further
+//   pieces, a fixed stride split over the waves of a workgroup and a
+//   fixed-order combine in LDS for a head. On the 16-byte vector path (rows of
+//   up to LMZ_SEG_FUSED_MAX_D columns) that happens in the walk's own launch
+//   (the fused launch below), otherwise in a second one (k_segsum_fix, from
+//   the desc[c] and npieces[c] that the walk then writes).
 // A chunk holds at most R positions (N is sized for U = min(K, u_cap)) and
 // reads at most R + T - 1 rows.
 //
@@ -65,7 +60,7 @@ namespace lmz {
 
 // Tuning knobs (overridable at build time).
 #ifndef LMZ_SEG_TDIV
-#define LMZ_SEG_TDIV 4               // long-segment threshold T = R / this (1..64)
+#define LMZ_SEG_TDIV 2               // long-segment threshold T = R / this (1..64)
 #endif
 #ifndef LMZ_SEG_RF4
 #define LMZ_SEG_RF4 4                // rows per gather batch with 4 vectors per lane
@@ -82,8 +77,14 @@ namespace lmz {
 #ifndef LMZ_SEG_RF2_LONG
 #define LMZ_SEG_RF2_LONG 16
 #endif
-#ifndef LMZ_SEG_SGD_ENDS
-#define LMZ_SEG_SGD_ENDS 2           // lm_segsum_sgd: segment ends (table rows) per gather batch
+#ifndef LMZ_SEG_SGD_ENDS4
+#define LMZ_SEG_SGD_ENDS4 2          // early updates: segment ends (table rows) per gather batch
+#endif                               // with 4, 2 and 1 vectors per lane
+#ifndef LMZ_SEG_SGD_ENDS2
+#define LMZ_SEG_SGD_ENDS2 4
+#endif
+#ifndef LMZ_SEG_SGD_ENDS1
+#define LMZ_SEG_SGD_ENDS1 6
 #endif
 #ifndef LMZ_SEG_SGD_RF4
 #define LMZ_SEG_SGD_RF4 3            // lm_segsum_sgd: rows per batch with 4 vectors per lane,
@@ -94,13 +95,7 @@ namespace lmz {
 #ifndef LMZ_SEG_FIX_RF
 #define LMZ_SEG_FIX_RF 16            // partial rows per wave in flight in the fix-up
 #endif
-#ifndef LMZ_SEG_WG_THREADS
-#define LMZ_SEG_WG_THREADS 64        // threads of a main-walk workgroup (one chunk per wave)
-#endif
-#ifndef LMZ_SEG_LDS_PAD
-#define LMZ_SEG_LDS_PAD 0            // LDS bytes reserved per workgroup (caps waves per CU)
-#endif
-constexpr int kSegThreads = LMZ_SEG_WG_THREADS;
+constexpr int kSegThreads = 256;     // threads of a workgroup: a chunk per wave
 constexpr int kSegWaves = kSegThreads / kWave;
 
 // Windows of positions a wave loads up front: [p0 - 1, p0 - 1 + 64 * NW)
@@ -110,33 +105,110 @@ constexpr int kSegWaves = kSegThreads / kWave;
 template <int R, int T>
 constexpr int windows_for() { return (R + T) / 64 + 1; }
 
-// Chunk bounds: the number of sorted positions whose running cost is below
-// t (the cost before position p of segment u is rw * p + ww * u), for
-// t = tA in lanes 0..31 and t = tB in lanes 32..63. A 32-ary search per
-// half-wave for the largest u < U with f(u) = rw * offsets[u] + ww * u <= t
-// (f(0) = 0), then b = offsets[u] + min(ceil((t - f(u)) / rw), len(u));
-// b = K once t >= rw * K + ww * U. Every value the search keeps is
-// wave-uniform. Besides b it returns that u and offsets[u], offsets[u + 1]:
-// b lies strictly inside segment u exactly when offsets[u] < b < offsets[u + 1].
+// Chunk bounds. A workgroup walks kSegWaves consecutive chunks, so its bounds
+// (targets t of the running cost) lie close together, and it looks for them
+// together: a 256-ary search (one probe per thread and round) keeps the types
+// that any of its targets can fall into, until they are few enough to load
+// their offsets into LDS: one round where there are at most types_cap of
+// them, two up to about 100K types. Each wave then finds its own two bounds
+// and, from the same offsets, every segment end of its chunk, without another
+// load. (A search per wave with 32 probes per target, and the segments from
+// inverse[perm[i]] for every position, had cost a chain of nine dependent
+// loads before the first gradient row, now five, and a 64-byte line per
+// gathered position.)
+template <int R>
+constexpr int types_cap() { return (kSegWaves * R / kSegThreads + 2) * kSegThreads; }
+
+// The chunks of a call, n <= a.nchunks of equal cost Q: the grid has room for
+// u_cap types; where far fewer turn up, n falls to a.enough, as long as no
+// chunk exceeds R positions (a cost of rw * R).
+struct Plan {
+  int n;
+  int64_t Q;
+};
+__device__ __forceinline__ Plan chunk_plan(const SegArgs& a, int U) {
+  const int Ub = U < a.u_cap ? U : static_cast<int>(a.u_cap);
+  const int64_t cost = int64_t(a.rw) * a.K + int64_t(a.ww) * Ub;
+  const int64_t most = int64_t(a.rw) * a.R;
+  const int64_t least = U > a.u_cap ? a.nchunks : (cost + most - 1) / most;
+  int n = a.enough > least ? a.enough : static_cast<int>(least);
+  if (n > a.nchunks) n = a.nchunks;
+  return Plan{n, (cost + n - 1) / n};
+}
+
+// The types [lo, lo + n) that hold every target from t_first to t_last (n <=
+// N), their offsets in s_win[0 .. n]. The cost before position p of segment u
+// is rw * p + ww * u, so the type of a target t is the largest u < U with
+// f(u) = rw * offsets[u] + ww * u <= t (f(0) = 0). Every thread of the
+// workgroup calls it. False where the offsets are inconsistent (the window
+// then holds some N types).
+template <int N>
+__device__ __forceinline__ bool load_window(const int32_t* __restrict__ offsets, int U, int rw,
+                                            int ww, int64_t t_first, int64_t t_last,
+                                            int (&s_win)[N + 1], int (&s_cnt)[2][kSegWaves],
+                                            int& lo_out, int& n_out) {
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  int lo = 0, n = U;
+  for (int round = 0; n > N && round < 8; ++round) {
+    const int st = (n - 1) / kSegThreads + 1;
+    const int64_t u = lo + int64_t(tid + 1) * st;
+    const bool in = u < int64_t(lo) + n;
+    const int64_t f = in ? int64_t(rw) * offsets[u] + int64_t(ww) * u : 0;
+    const uint64_t first = ballot(in && f <= t_first), last = ballot(in && f <= t_last);
+    if (lane == 0) {
+      s_cnt[0][wave] = __popcll(first);
+      s_cnt[1][wave] = __popcll(last);
+    }
+    __syncthreads();
+    int c0 = 0, c1 = 0;
+#pragma unroll
+    for (int w = 0; w < kSegWaves; ++w) {
+      c0 += s_cnt[0][w];
+      c1 += s_cnt[1][w];
+    }
+    __syncthreads();
+    c0 = first_lane(c0);
+    c1 = first_lane(c1);
+    const int64_t end = lo + (int64_t(c1) + 1) * st;
+    const int64_t most = int64_t(lo) + n;
+    lo += c0 * st;
+    n = static_cast<int>((end < most ? end : most) - lo);
+    if (n < 1) n = 1;  // only inconsistent offsets
+  }
+  const bool ok = n <= N;
+  if (!ok) n = N;
+  for (int i = tid; i <= n; i += kSegThreads) s_win[i] = offsets[lo + i];
+  __syncthreads();
+  lo_out = lo;
+  n_out = n;
+  return ok;
+}
+
+// The bound of a target: the number of sorted positions whose running cost is
+// below t, for t = tA in lanes 0..31 and t = tB in lanes 32..63: with u as
+// above, b = offsets[u] + min(ceil((t - f(u)) / rw), len(u)); b = K once
+// t >= rw * K + ww * U. A 32-ary search of the window per half-wave. Besides b
+// it returns that u and offsets[u], offsets[u + 1]: b lies strictly inside
+// segment u exactly when offsets[u] < b < offsets[u + 1].
 struct Bound {
   int b, u, o0, o1;
 };
-__device__ __forceinline__ void chunk_bounds(const int32_t* __restrict__ offsets, int U, int rw,
-                                             int ww, int K, int64_t tA, int64_t tB, Bound& A,
-                                             Bound& B) {
+template <int N>
+__device__ __forceinline__ void chunk_bounds(const int (&s_win)[N + 1], int lo, int n, int U,
+                                             int rw, int ww, int K, int64_t tA, int64_t tB,
+                                             Bound& A, Bound& B) {
   const int lane = lane_id();
   const bool hi = lane >= 32;
   const int hl = lane & 31;
-  int loA = 0, nA = U, loB = 0, nB = U;
+  const int64_t t = (hi ? tB : tA) - int64_t(ww) * lo;
+  int loA = 0, nA = n, loB = 0, nB = n;
   while (nA > 1 || nB > 1) {
     const int sA = (nA + 31) / 32, sB = (nB + 31) / 32;
-    const int lo = hi ? loB : loA, n = hi ? nB : nA, st = hi ? sB : sA;
-    const int64_t t = hi ? tB : tA;
-    const int u = lo + (hl + 1) * st;
-    bool le = false;
-    if (n > 1 && u < lo + n) le = int64_t(rw) * offsets[u] + int64_t(ww) * u <= t;
-    const uint64_t m = ballot(le);
-    const int cA = __popcll(m & 0xffffffffull), cB = __popcll(m >> 32);
+    const int l = hi ? loB : loA, m = hi ? nB : nA, st = hi ? sB : sA;
+    const int u = l + (hl + 1) * st;
+    const bool le = m > 1 && u < l + m && int64_t(rw) * s_win[u < n ? u : n] + int64_t(ww) * u <= t;
+    const uint64_t b = ballot(le);
+    const int cA = __popcll(b & 0xffffffffull), cB = __popcll(b >> 32);
     if (nA > 1) {
       loA += cA * sA;
       nA = nA - cA * sA < sA ? nA - cA * sA : sA;
@@ -147,44 +219,67 @@ __device__ __forceinline__ void chunk_bounds(const int32_t* __restrict__ offsets
     }
   }
   const int u = hi ? loB : loA;
-  const int64_t t = hi ? tB : tA;
-  const int o0 = offsets[u], o1 = offsets[u + 1];
+  const int o0 = s_win[u], o1 = s_win[u + 1];
   const int64_t into = (t - (int64_t(rw) * o0 + int64_t(ww) * u) + rw - 1) / rw;
   int b = int64_t(o0) + into < int64_t(o1) ? static_cast<int>(int64_t(o0) + into) : o1;
-  if (t >= int64_t(rw) * K + int64_t(ww) * U) b = K;
-  A = Bound{first_lane(b), first_lane(u), first_lane(o0), first_lane(o1)};
-  B = Bound{read_lane(b, 32), read_lane(u, 32), read_lane(o0, 32), read_lane(o1, 32)};
+  if (t + int64_t(ww) * lo >= int64_t(rw) * K + int64_t(ww) * U) b = K;
+  A = Bound{first_lane(b), first_lane(u) + lo, first_lane(o0), first_lane(o1)};
+  B = Bound{read_lane(b, 32), read_lane(u, 32) + lo, read_lane(o0, 32), read_lane(o1, 32)};
 }
 
 // ---------------------------------------------------------------------------
-// Fused launch: fix-up workgroups after the walk's in the same grid.
-// Workgroups are dispatched in the order of their index (per XCD), so every
-// walk workgroup holds a slot or has finished before a fix-up workgroup
-// starts; walk workgroups never wait, so a fix-up's wait for their flags
-// always ends (bounded all the same: LM_DEVERR_SPIN). Partial rows and
-// descriptors go out as agent-scope stores (coherent across the XCDs'
-// L2s), the walk waits for them before it sets its flag to the call's
-// epoch, and the fix-up reads them with agent-scope loads once the flag
-// holds that epoch: no workspace contents need clearing between calls.
-// Rows wider than one walk tile (1024 columns) take one flag per chunk and
-// tile: workgroup b of the walk is column tile b % tiles of chunks
-// (b / tiles) * 4 ..., and a fix-up tile of 256 columns, which lies inside
-// one walk tile, waits for that tile's flags (tile 0's also covers the
-// chunk's descriptor).
+// Fused launch: the fix-up in the walk's launch.
+// Partial rows go out as agent-scope stores (coherent across the XCDs' L2s),
+// the walk waits for them before it says so in a word per chunk and column
+// tile, and they are read with agent-scope loads. A word holds a tag that is
+// new for every call (of a per-process counter) above its count and flag, so
+// no workspace contents need clearing between calls (word_add).
+//   A segment of fewer than kHeadPieces further pieces: the wave that adds the
+//   last of its pieces to the count in the word of the segment's first chunk
+//   sums them all, in order. No wave waits for another.
+//   A longer one (a head of the Zipf law): every piece sets the flag in its
+//   own chunk's word, and a fix-up workgroup per column tile of 256, after the
+//   walk's workgroups in the same grid, waits for them and sums them with all
+//   its waves. Workgroups are dispatched in the order of their index (per
+//   XCD), so every walk workgroup holds a slot or has finished before a
+//   fix-up workgroup starts; walk workgroups never wait, so a fix-up's wait
+//   always ends (bounded all the same: LM_DEVERR_SPIN). A head reaches over
+//   the end of the span of kHeadPieces chunks it starts in, so the workgroups
+//   of a span find it with one search for that bound, while the walk runs.
+// Fix-up workgroups for every segment, each looking after 4 chunks, had cost
+// more than the sums: at 30,011 ids over 50K words, D = 650, 8 of 39 us.
+// Workgroup b of the walk is column tile b % tiles of chunks (b / tiles) * 4
+// ..., and a fix-up tile of 256 columns lies inside one walk tile.
 // ---------------------------------------------------------------------------
-constexpr int kFusedThreads = 256;
-constexpr int kFusedWaves = kFusedThreads / kWave;
-#ifndef LMZ_SEG_FUSED_SPAN
-#define LMZ_SEG_FUSED_SPAN 4         // chunks a fused fix-up workgroup looks after (<= 64)
-#endif
 #ifndef LMZ_SEG_FUSED_RF
-#define LMZ_SEG_FUSED_RF 8           // pieces per wave per round in the fused fix-up
+#define LMZ_SEG_FUSED_RF 16          // pieces per wave per round in the fused fix-up
 #endif
 #ifndef LMZ_SEG_FUSED_SLEEP
 #define LMZ_SEG_FUSED_SLEEP 8        // s_sleep argument (x 64 cycles) between flag polls
 #endif
-constexpr int kFusedSpan = LMZ_SEG_FUSED_SPAN;
-static_assert(kFusedSpan <= kWave, "one descriptor per lane");
+constexpr int kHeadPieces = 16;  // further pieces from which a segment is a head
+// A chunk's word: the tag, a flag and a count.
+constexpr int kTagShift = 20;
+constexpr uint64_t kPieceFlag = 1u << 19;
+constexpr uint32_t kCountMask = (1u << 19) - 1;
+
+// Add to a chunk's word, which may still hold what an earlier call (or other
+// data) left: returns its flag and count after the addition.
+__device__ __forceinline__ uint32_t word_add(uint64_t* w, uint64_t tag, uint64_t x) {
+  constexpr uint64_t kLow = (1u << kTagShift) - 1;
+  uint64_t old = add_agent(w, x);
+  while ((old >> kTagShift) != tag) {  // ends: a failed exchange is another's success
+    uint64_t cur = ld_agent(w);
+    if ((cur >> kTagShift) == tag) {
+      old = add_agent(w, x);
+    } else if (__hip_atomic_compare_exchange_strong(w, &cur, (tag << kTagShift) | x,
+                                                    __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT)) {
+      return static_cast<uint32_t>(x);
+    }
+  }
+  return static_cast<uint32_t>((old & kLow) + x);
+}
 
 // The output row of type s: s itself, or row_ids[s] for lm_segsum_rows
 // (-1 when that id lies outside [0, out_rows); LM_DEVERR_ID_RANGE is raised
@@ -231,31 +326,33 @@ __device__ __forceinline__ void table_vec(__amdgpu_buffer_rsrc_t rs, int col, fl
   }
 }
 
-// Finish VEC columns from col of type row orow: out = sum, or the table
-// row (and Adam's moments) updated with it.
+// VEC columns of a type row, at offset off into the output: written with the
+// sums, or (load, then finish) the table row and Adam's moments updated.
 template <int VEC, int OP>
-__device__ __forceinline__ void finish_row(const SegArgs& a, int64_t orow, int col, float* sum) {
-  const int64_t off = orow * a.ld_out + col;
-  if constexpr (OP == kOpSgd) {
-    float p[VEC];
-    load_vec<VEC>(a.out + off, p);
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) sgd_value(p[e], sum[e], a.opt);
-    store_vec<VEC>(a.out + off, p);
-  } else if constexpr (OP == kOpAdam) {
-    float p[VEC], m[VEC], v[VEC];
-    load_vec<VEC>(a.out + off, p);
-    load_vec<VEC>(a.m + off, m);
-    load_vec<VEC>(a.v + off, v);
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) adam_value(p[e], m[e], v[e], sum[e], a.opt);
-    store_vec<VEC>(a.out + off, p);
-    store_vec<VEC>(a.m + off, m);
-    store_vec<VEC>(a.v + off, v);
-  } else {
-    store_vec<VEC>(a.out + off, sum);
+struct TableVec {
+  float p[OP == kOpStore ? 1 : VEC], m[OP == kOpAdam ? VEC : 1], v[OP == kOpAdam ? VEC : 1];
+  __device__ __forceinline__ void load(const SegArgs& a, int64_t off) {
+    if constexpr (OP != kOpStore) load_vec<VEC>(a.out + off, p);
+    if constexpr (OP == kOpAdam) {
+      load_vec<VEC>(a.m + off, m);
+      load_vec<VEC>(a.v + off, v);
+    }
   }
-}
+  __device__ __forceinline__ void finish(const SegArgs& a, int64_t off, const float* sum) {
+    if constexpr (OP == kOpSgd) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) sgd_value(p[e], sum[e], a.opt);
+    } else if constexpr (OP == kOpAdam) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) adam_value(p[e], m[e], v[e], sum[e], a.opt);
+    }
+    store_vec<VEC>(a.out + off, OP == kOpStore ? sum : p);
+    if constexpr (OP == kOpAdam) {
+      store_vec<VEC>(a.m + off, m);
+      store_vec<VEC>(a.v + off, v);
+    }
+  }
+};
 
 // Columns. A lane's vector starts at column col; past the last whole vector
 // of a row it is the row's last VEC columns instead, so that no load leaves
@@ -270,21 +367,6 @@ __device__ __forceinline__ int vec_col(int col, int D) {
   return col < D ? col : D - VEC;
 }
 
-// As finish_row, from the vector at col_ld, for the columns from col on: in
-// the fix-up the repeated columns may be another workgroup's, which updates
-// them.
-template <int VEC, int OP, bool TAIL>
-__device__ __forceinline__ void finish_cols(const SegArgs& a, int64_t orow, int col, int col_ld,
-                                            float* sum) {
-  if (!TAIL || col == col_ld) {
-    finish_row<VEC, OP>(a, orow, col, sum);
-  } else {
-#pragma unroll
-    for (int e = 0; e < VEC; ++e)
-      if (col_ld + e >= col) finish_row<1, OP>(a, orow, col_ld + e, sum + e);
-  }
-}
-
 // Partial rows at agent scope: pairs of columns, or single ones where D is no
 // multiple of a vector (the rows of the workspace are D values apart).
 template <int VEC>
@@ -296,27 +378,40 @@ __device__ __forceinline__ void store_vec_agent(float* p, const float* v) {
              uint64_t(__float_as_uint(v[i])) | (uint64_t(__float_as_uint(v[i + 1])) << 32));
 }
 
-template <bool TAIL>
-__device__ __forceinline__ void load4_agent(const float* p, float* v) {
-  if constexpr (TAIL) {
+template <int VEC, bool TAIL>
+__device__ __forceinline__ void load_vec_agent(const float* p, float* v) {
+  if constexpr (TAIL || VEC % 2 != 0) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+    for (int e = 0; e < VEC; ++e)
       v[e] = __uint_as_float(ld_agent(reinterpret_cast<const uint32_t*>(p) + e));
-    return;
+  } else {
+#pragma unroll
+    for (int e = 0; e < VEC; e += 2) {
+      const uint64_t x = ld_agent(reinterpret_cast<const uint64_t*>(p + e));
+      v[e] = __uint_as_float(static_cast<uint32_t>(x));
+      v[e + 1] = __uint_as_float(static_cast<uint32_t>(x >> 32));
+    }
   }
-  const uint64_t x = ld_agent(reinterpret_cast<const uint64_t*>(p));
-  const uint64_t y = ld_agent(reinterpret_cast<const uint64_t*>(p) + 1);
-  v[0] = __uint_as_float(static_cast<uint32_t>(x));
-  v[1] = __uint_as_float(static_cast<uint32_t>(x >> 32));
-  v[2] = __uint_as_float(static_cast<uint32_t>(y));
-  v[3] = __uint_as_float(static_cast<uint32_t>(y >> 32));
 }
 
-// Every lane of the wave calls this; the lanes with need wait until
-// flags[idx] holds the epoch. False if the wait gave up.
-__device__ __forceinline__ bool wait_flags(const SegArgs& a, int idx, bool need) {
+// The partial row of piece t of the segment that starts in chunk cs.
+__device__ __forceinline__ float* piece_row(const SegArgs& a, int cs, int t) {
+  return t == 0 ? a.part_start + static_cast<int64_t>(cs) * a.D
+                : a.part_cont + static_cast<int64_t>(cs + t) * a.D;
+}
+
+template <int NV>
+constexpr int ends_for() {
+  return NV >= 4 ? LMZ_SEG_SGD_ENDS4 : NV == 2 ? LMZ_SEG_SGD_ENDS2 : LMZ_SEG_SGD_ENDS1;
+}
+
+// Every lane of the wave calls this; the lanes with need wait until chunk x's
+// word (of column tile ct) says that its piece is there. False if the wait
+// gave up.
+__device__ __forceinline__ bool wait_piece(const SegArgs& a, int x, int ct, bool need) {
   for (uint32_t spin = 0;; ++spin) {
-    const bool ok = !need || ld_agent(a.flags + idx) == a.wait_epoch;
+    const uint64_t f = need ? ld_agent(a.flags + size_t(x) * a.tiles + ct) : 0;
+    const bool ok = !need || ((f >> kTagShift) == a.wait_tag && (f & kPieceFlag));
     if (!ballot(!ok)) return true;
     if (spin >= a.spin_limit) {
       if (lane_id() == 0) raise_err(a.dev_err, LM_DEVERR_SPIN);
@@ -326,120 +421,83 @@ __device__ __forceinline__ bool wait_flags(const SegArgs& a, int idx, bool need)
   }
 }
 
-// Fix-up workgroup f: chunks [c0, c0 + kFusedSpan) of span f / fix_tiles,
-// columns of tile f % fix_tiles. It waits for the span's descriptors, then
-// sums each long segment that starts there as k_segsum_fix does (one wave
-// for fewer than 16 further pieces, all waves and an LDS combine for a
-// head), waiting for each piece's flag before loading it.
+// Fix-up workgroup f: the head, if any, that starts in chunks [c0, c0 +
+// kHeadPieces) of span f / fix_tiles, columns of tile f % fix_tiles: wave w
+// adds pieces w, w + W, ... in order, and the waves' sums are added in order.
 template <int OP, bool TAIL>
 __device__ __forceinline__ void fused_fix(const SegArgs& a) {
   constexpr int RF = LMZ_SEG_FUSED_RF;
-  constexpr int kShortMax = 16;  // further pieces below this: one wave
-  __shared__ float s_part[kFusedWaves][kFusedCols];
+  constexpr int kTypes = 2 * kSegThreads;
+  __shared__ float s_part[kSegWaves][kFusedCols];
+  __shared__ int s_win[kTypes + 1];
+  __shared__ int s_cnt[2][kSegWaves];
   const int lane = lane_id();
   const int wave = first_lane(static_cast<int>(threadIdx.x >> 6));
   const int f = static_cast<int>(blockIdx.x) - a.main_blocks;
-  const int c0 = (f / a.fix_tiles) * kFusedSpan;
-  const int nc = a.nchunks - c0 < kFusedSpan ? a.nchunks - c0 : kFusedSpan;
-  const int D = a.D;
-  const int col = (f % a.fix_tiles) * kFusedCols + lane * 4;
+  const int c0 = (f / a.fix_tiles) * kHeadPieces, K = a.K, D = a.D;
+  const int tile0 = (f % a.fix_tiles) * kFusedCols, col = tile0 + lane * 4;
   const int col_ld = vec_col<4, TAIL>(col, D);
-  // The walk's column tile these columns belong to (a fix-up tile of
-  // kFusedCols columns never straddles two), and the flag of chunk x's part
-  // of it; tile 0's flag also covers x's descriptor.
-  const int wt = (f % a.fix_tiles) * kFusedCols / a.tile_cols;
-  auto flag_of = [&](int x, int t) { return x * a.tiles + t; };
-  const int U = first_lane(static_cast<int>(*a.num_unique));
-
-  // Wave 0 waits for the span and reads its descriptors once; every wave
-  // takes them from LDS, so all agree on the heads (and on the barriers).
-  __shared__ int s_desc[kWave], s_np[kWave];
-  const bool mine = lane < nc;
-  const int ci = c0 + (mine ? lane : 0);
-  if (wave == 0) {
-    wait_flags(a, flag_of(ci, 0), mine);
-    s_desc[lane] = mine ? ld_agent(a.desc + ci) : -1;
-    s_np[lane] = mine ? ld_agent(a.npieces + ci) : 0;
+  const int ct = tile0 / a.tile_cols;  // the walk's column tile that holds this one
+  const int64_t U64 = *a.num_unique;
+  const int U = first_lane(static_cast<int>(U64 < K ? U64 : K));
+  if (U < 1) return;
+  // The segment that lies across the end of the span, if any.
+  const Plan plan = chunk_plan(a, U);
+  const int64_t Q = plan.Q, t_end = int64_t(c0 + kHeadPieces) * Q;
+  if (c0 + kHeadPieces >= plan.n) return;
+  int lo, nt;
+  load_window<kTypes>(a.offsets, U, a.rw, a.ww, t_end, t_end, s_win, s_cnt, lo, nt);
+  Bound A, B;
+  chunk_bounds<kTypes>(s_win, lo, nt, U, a.rw, a.ww, K, t_end, t_end, A, B);
+  const int64_t cs64 = (int64_t(a.rw) * A.o0 + int64_t(a.ww) * A.u) / Q;
+  const int64_t ce64 = (int64_t(a.rw) * (A.o1 - 1) + int64_t(a.ww) * A.u) / Q;
+  const int last = plan.n - 1;
+  const int cs = static_cast<int>(cs64 < c0 ? -1 : (cs64 > last ? last : cs64));
+  const int ce = static_cast<int>(ce64 > last ? last : ce64);
+  const int P = ce - cs, s = A.u;
+  if (A.b <= A.o0 || A.b >= A.o1 || cs < 0 || P < kHeadPieces || s >= a.u_cap) return;
+  // The type's row, before the wait (no other workgroup writes these columns).
+  const int64_t orow = out_row_of(a, s);
+  const int cx = tile0 + static_cast<int>(threadIdx.x);
+  TableVec<1, OP> tv;
+  if (orow >= 0) tv.load(a, orow * a.ld_out + (cx < D ? cx : D - 1));
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int t0 = wave; t0 <= P; t0 += kSegWaves * RF) {
+    const int tl = t0 + (lane < RF ? lane : 0) * kSegWaves;  // lane r: piece t0 + r * W
+    wait_piece(a, cs + (tl <= P ? tl : 0), ct, lane < RF && tl <= P);
+    float buf[RF][4];
+#pragma unroll
+    for (int r = 0; r < RF; ++r) {
+      const int t = t0 + r * kSegWaves;
+      load_vec_agent<4, TAIL>(piece_row(a, cs, t <= P ? t : t0) + col_ld, buf[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < RF; ++r)
+      if (t0 + r * kSegWaves <= P)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += buf[r][e];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (TAIL) {  // this lane's own columns within the tile
+      const int x = col_ld + e - tile0;
+      if (x >= lane * 4) s_part[wave][x] = acc[e];
+    } else {
+      s_part[wave][lane * 4 + e] = acc[e];
+    }
   }
   __syncthreads();
-  const int sd = s_desc[lane], np = s_np[lane];
-  const bool has = sd >= 0 && sd < U && sd < a.u_cap && np >= 1 && np <= a.nchunks - 1 - ci;
-  const uint64_t todo = ballot(has);
-  const uint64_t heads = ballot(has && np >= kShortMax);
-  auto piece = [&](int cs, int t) {
-    return (t == 0 ? a.part_start + static_cast<int64_t>(cs) * D
-                   : a.part_cont + static_cast<int64_t>(cs + t) * D) + col_ld;
-  };
-
-  // Shorter long segments: the j-th to wave j % kFusedWaves.
-  int j = 0;
-  for (uint64_t m = todo & ~heads; m; m &= m - 1, ++j) {
-    if (j % kFusedWaves != wave) continue;
-    const int i = __builtin_ctzll(m);
-    const int cs = c0 + i, s = read_lane(sd, i), P = read_lane(np, i);
-    wait_flags(a, flag_of(cs + (lane <= P ? lane : 0), wt), lane <= P);
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int t0 = 0; t0 <= P; t0 += RF) {
-      float buf[RF][4];
+  if (cx < D && orow >= 0) {
+    float sum = 0.f;
 #pragma unroll
-      for (int r = 0; r < RF; ++r) load4_agent<TAIL>(piece(cs, t0 + r <= P ? t0 + r : 0), buf[r]);
-#pragma unroll
-      for (int r = 0; r < RF; ++r)
-        if (t0 + r <= P)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[e] += buf[r][e];
-    }
-    const int64_t orow = out_row_of(a, s);
-    if (col < D && orow >= 0) finish_cols<4, OP, TAIL>(a, orow, col, col_ld, acc);
-  }
-
-  // Heads, one after the other, all waves: wave w adds pieces w, w + W, ...
-  for (uint64_t m = heads; m; m &= m - 1) {
-    const int i = __builtin_ctzll(m);
-    const int cs = c0 + i, s = read_lane(sd, i), P = read_lane(np, i);
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int t0 = wave; t0 <= P; t0 += kFusedWaves * RF) {
-      const int tl = t0 + (lane < RF ? lane : 0) * kFusedWaves;  // lane r: piece t0 + r * W
-      wait_flags(a, flag_of(cs + (tl <= P ? tl : 0), wt), lane < RF && tl <= P);
-      float buf[RF][4];
-#pragma unroll
-      for (int r = 0; r < RF; ++r) {
-        const int t = t0 + r * kFusedWaves;
-        load4_agent<TAIL>(piece(cs, t <= P ? t : t0), buf[r]);
-      }
-#pragma unroll
-      for (int r = 0; r < RF; ++r)
-        if (t0 + r * kFusedWaves <= P)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[e] += buf[r][e];
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if constexpr (TAIL) {  // this lane's own columns within the tile
-        const int x = col_ld + e - (col - lane * 4);
-        if (x >= lane * 4) s_part[wave][x] = acc[e];
-      } else {
-        s_part[wave][lane * 4 + e] = acc[e];
-      }
-    }
-    __syncthreads();
-    const int64_t orow = out_row_of(a, s);
-    for (int x = threadIdx.x; x < kFusedCols; x += kFusedThreads) {
-      const int cx = (f % a.fix_tiles) * kFusedCols + x;
-      if (cx < D && orow >= 0) {
-        float sum = 0.f;
-#pragma unroll
-        for (int w = 0; w < kFusedWaves; ++w) sum += s_part[w][x];
-        finish_row<1, OP>(a, orow, cx, &sum);
-      }
-    }
-    __syncthreads();
+    for (int w = 0; w < kSegWaves; ++w) sum += s_part[w][threadIdx.x];
+    tv.finish(a, orow * a.ld_out + cx, &sum);
   }
 }
 
-template <typename GT, int VEC, int NV, int RF, int R, int T, int NTHR, bool FUSED, int OP,
+template <typename GT, int VEC, int NV, int RF, int R, int T, bool FUSED, int OP,
           bool TAIL, bool EARLY>
-__global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
+__global__ __launch_bounds__(kSegThreads) void k_segsum(SegArgs a) {
   if constexpr (FUSED) {
     if (static_cast<int>(blockIdx.x) >= a.main_blocks) {
       fused_fix<OP, TAIL>(a);
@@ -457,15 +515,15 @@ __global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
   // column tile = block % tiles; otherwise the tile is blockIdx.y.
   const int blk = FUSED ? static_cast<int>(blockIdx.x) / a.tiles : static_cast<int>(blockIdx.x);
   const int ct = FUSED ? static_cast<int>(blockIdx.x) % a.tiles : static_cast<int>(blockIdx.y);
-  const int c = first_lane(blk * (NTHR / kWave) + static_cast<int>(threadIdx.x >> 6));
-  if (c >= a.nchunks) return;
-  // Fused launch: once this chunk's descriptor and partial rows are visible
-  // at agent scope (written with agent-scope stores, then waited for),
-  // flags[c] says so to the fix-up workgroups.
-  auto publish = [&]() {
-    if constexpr (FUSED) {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      if (lane_id() == 0) st_agent(a.flags + size_t(c) * a.tiles + ct, a.epoch);
+  const int wave = first_lane(static_cast<int>(threadIdx.x >> 6));
+  const int c0 = blk * kSegWaves, c = c0 + wave;
+  // Two launches: the long segment that starts in this chunk, for the fix-up.
+  auto describe = [&](int s, int np) {
+    if constexpr (!FUSED) {
+      if (ct == 0 && lane == 0) {
+        a.desc[c] = s;
+        a.npieces[c] = np;
+      }
     }
   };
   const int K = a.K, D = a.D;
@@ -475,22 +533,34 @@ __global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
   if (U64 > a.u_cap && c == 0 && ct == 0 && lane == 0) raise_err(a.dev_err, LM_DEVERR_CAPACITY);
   const int U = first_lane(static_cast<int>(U64 < K ? U64 : K));
   if (U < 1) {  // K > 0 always has a type: only a bad count gets here
-    if (ct == 0 && lane == 0) {
-      st_agent(a.desc + c, -1);
-      st_agent(a.npieces + c, 0);
-      if (c == 0) raise_err(a.dev_err, LM_DEVERR_CAPACITY);
-    }
-    publish();
+    if (c < a.nchunks) describe(-1, 0);
+    if (c == 0 && ct == 0 && lane == 0) raise_err(a.dev_err, LM_DEVERR_CAPACITY);
     return;
   }
-  const int Ub = U < a.u_cap ? U : static_cast<int>(a.u_cap);
-  const int64_t cost = int64_t(a.rw) * K + int64_t(a.ww) * Ub;
-  const int64_t Q = (cost + a.nchunks - 1) / a.nchunks;
+  const Plan plan = chunk_plan(a, U);
+  const int nchunks = plan.n;
+  const int64_t Q = plan.Q;
+  if (c0 >= nchunks) {
+    if (c < a.nchunks) describe(-1, 0);
+    return;
+  }
+  constexpr int kTypes = types_cap<R>();
+  __shared__ int s_win[kTypes + 1];
+  __shared__ int s_cnt[2][kSegWaves];
+  __shared__ uint32_t s_ends[kSegWaves][2 * NW];
+  int lo, nt;
+  const int c_last = c0 + kSegWaves < nchunks ? c0 + kSegWaves : nchunks;
+  bool bad = !load_window<kTypes>(a.offsets, U, a.rw, a.ww, int64_t(c0) * Q, int64_t(c_last) * Q,
+                                  s_win, s_cnt, lo, nt);
+  if (c >= nchunks) {  // no barrier below
+    if (c < a.nchunks) describe(-1, 0);
+    return;
+  }
   Bound A, B;
-  chunk_bounds(a.offsets, U, a.rw, a.ww, K, int64_t(c) * Q, int64_t(c + 1) * Q, A, B);
+  chunk_bounds<kTypes>(s_win, lo, nt, U, a.rw, a.ww, K, int64_t(c) * Q, int64_t(c + 1) * Q, A, B);
   const int p0 = A.b;
   int p1 = B.b;
-  bool cut_after = c < a.nchunks - 1;  // p1 is a cut of the cost, not the end of the positions
+  bool cut_after = c < nchunks - 1;  // p1 is a cut of the cost, not the end of the positions
   if (!cut_after) p1 = K;
   if (p1 - p0 > R) {  // only inconsistent offsets: never walk past the windows
     if (lane == 0) raise_err(a.dev_err, LM_DEVERR_CAPACITY);
@@ -498,11 +568,7 @@ __global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
     cut_after = false;
   }
   if (p1 <= p0) {  // an empty chunk (a segment end cost more than Q)
-    if (ct == 0 && lane == 0) {
-      st_agent(a.desc + c, -1);
-      st_agent(a.npieces + c, 0);
-    }
-    publish();
+    describe(-1, 0);
     return;
   }
 
@@ -515,66 +581,87 @@ __global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
   const int s_l = B.u, len_l = B.o1 - B.o0;
   const bool long_f = started_before && len_f >= T;
   const bool long_l = cont_after && len_l >= T;
-  if (ct == 0 && lane == 0) {
-    // A long segment that starts in this chunk ends in the chunk of its last
-    // position, whose cost is rw * (offsets[s_l + 1] - 1) + ww * s_l.
-    const bool starts_long = long_l && !(started_before && s_l == s_f);
-    int np = 0;
-    if (starts_long) {
-      int64_t ce = (int64_t(a.rw) * (B.o1 - 1) + int64_t(a.ww) * s_l) / Q;
-      if (ce > a.nchunks - 1) ce = a.nchunks - 1;
-      np = static_cast<int>(ce - c);
-    }
-    st_agent(a.desc + c, starts_long && np >= 1 ? s_l : -1);
-    st_agent(a.npieces + c, np);
+  const bool starts_long = long_l && !(started_before && s_l == s_f);
+  // The chunk of a sorted position p of type s: that of its cost.
+  auto chunk_of = [&](int p, int s) {
+    const int64_t x = (int64_t(a.rw) * p + int64_t(a.ww) * s) / Q;
+    return static_cast<int>(x < 0 ? 0 : (x < nchunks ? x : nchunks - 1));
+  };
+  if constexpr (!FUSED) {
+    const int np = starts_long ? chunk_of(B.o1 - 1, s_l) - c : 0;
+    describe(np >= 1 ? s_l : -1, np);
   }
   // Rows this chunk sums: skip a short segment owned by the previous chunk,
   // run a short last segment to its end, stop a long one at p1.
   const int q = started_before && !long_f ? A.o1 : p0;
   int q_end = cont_after && !long_l ? B.o1 : p1;
   const int walk_max = p0 - 1 + NW * kWave - 1;  // last position whose end bit is known
-  bool bad = false;
   if (q_end > walk_max) {
     bad = true;  // only inconsistent offsets get here: never walk past the windows
     q_end = walk_max;
   }
 
-  // 2. Gather the permutation and the segment of every position in the
-  //    windows (sentinels: -2 before position 0, -1 from position K on).
-  //    The loads are unconditional, at clamped positions: a load under a
-  //    lane condition makes the compiler wait for every load before it.
-  //    The windows cover the longest chunk; the walk reads rows q ..
-  //    q_end - 1, and the end bit of row q_end - 1 needs the segment of
-  //    position q_end, so past q_end every lane repeats it (one line, a
-  //    cache hit) instead of fetching positions no row uses.
-  int pw[NW], sw[NW];
-  auto win_pos = [&](int w) {
-    const int p = p0 - 1 + w * kWave + lane;
-    return p < q_end ? p : q_end;
-  };
+  // 2. The permutation of the windows' positions. The loads are unconditional,
+  //    at clamped positions: a load under a lane condition makes the compiler
+  //    wait for every load before it. The windows cover the longest chunk; past
+  //    q_end every lane repeats that position (one line, a cache hit).
+  int pw[NW];
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
-    const int pos = win_pos(w);
+    int pos = p0 - 1 + w * kWave + lane;
+    pos = pos < q_end ? pos : q_end;
     pw[w] = a.perm[pos < 0 ? 0 : (pos < K ? pos : K - 1)];
   }
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    const int pos = win_pos(w);
-    const bool ok = pos >= 0 && pos < K;
-    const bool kin = static_cast<uint32_t>(pw[w]) < static_cast<uint32_t>(K);
-    bad |= ok && !kin;
-    if (!kin) pw[w] = 0;
-    const int sv = a.inverse[pw[w]];
-    sw[w] = ok ? sv : (pos < 0 ? -2 : -1);
+  //    The chunk's word too, so that its tag is this call's by the time a piece
+  //    is done.
+  uint64_t* const word = a.flags + size_t(c) * a.tiles + ct;
+  uint64_t word0 = 0;
+  if constexpr (FUSED) {
+    if ((long_f || long_l) && lane == 0) word0 = ld_agent(word);
   }
-  // ends[w] bit j: position p0-1+64w+j is the last of its segment.
+  //    While it flies: ends[w] bit j: position p0-1+64w+j is the last of its
+  //    segment, from the offsets in LDS (type A.u + i ends before
+  //    offsets[A.u + i + 1]; a chunk holds at most R + 2 types), and sw[w], the
+  //    type of each position: A.u plus the ends before it.
+#pragma unroll
+  for (int i = 0; i < 2 * NW; i += kWave)
+    if (lane + i < 2 * NW) s_ends[wave][lane + i] = 0;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+  for (int i = 0; i < R + 2; i += kWave) {
+    const int u = A.u - lo + i + lane;
+    if (u < nt) {
+      const int j = s_win[u + 1] - p0;
+      if (static_cast<uint32_t>(j) < static_cast<uint32_t>(NW * kWave))
+        atomicOr(&s_ends[wave][j >> 5], 1u << (j & 31));
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   uint64_t ends[NW];
+  int sw[NW];
+  int before = A.u;
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
-    int nxt = __shfl_down(sw[w], 1, kWave);
-    if (lane == kWave - 1) nxt = w + 1 < NW ? read_lane(sw[w + 1 < NW ? w + 1 : w], 0) : -3;
-    ends[w] = ballot(sw[w] != nxt);
+    const uint32_t e0 = static_cast<uint32_t>(first_lane(s_ends[wave][2 * w]));
+    const uint32_t e1 = static_cast<uint32_t>(first_lane(s_ends[wave][2 * w + 1]));
+    ends[w] = (uint64_t(e1) << 32) | e0;
+    sw[w] = before + popc_below(ends[w]);
+    before += __popcll(ends[w]);
   }
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    if (static_cast<uint32_t>(pw[w]) >= static_cast<uint32_t>(K)) {
+      bad = true;
+      pw[w] = 0;
+    }
+  }
+  if constexpr (FUSED) {
+    if ((long_f || long_l) && lane == 0 && (word0 >> kTagShift) != a.tag)
+      __hip_atomic_compare_exchange_strong(word, &word0, a.tag << kTagShift, __ATOMIC_RELAXED,
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // The map of the tokens either side of p0 (the arrays' consistency, below).
+  const int at_p0 = a.inverse[lane == 0 ? read_lane(pw[0], 0) : read_lane(pw[0], 1)];
   // lm_segsum_rows: the output row of every position's type, gathered with
   // the windows (the first segment end needs it, not the first row loads);
   // -1 marks an id outside [0, out_rows) (and clamped positions).
@@ -658,7 +745,7 @@ __global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
   const GT* __restrict__ grad = static_cast<const GT*>(a.grad);
   bool bad_row = false;
   // EARLY: segment ends, and so table rows, per batch.
-  constexpr int kEnds = EARLY ? LMZ_SEG_SGD_ENDS : 1;
+  constexpr int kEnds = !EARLY ? 1 : ends_for<NV>();
   static_assert(kEnds >= 1 && kEnds <= RF, "table rows per batch");
 
 #pragma unroll
@@ -768,12 +855,65 @@ __global__ __launch_bounds__(NTHR) void k_segsum(SegArgs a) {
     }
   }
   // Report a segment map that disagrees with offsets at the chunk start.
-  const int seg_before = read_lane(sw[0], 0), seg_p0 = read_lane(sw[0], 1);
+  const int seg_before = p0 > 0 ? read_lane(at_p0, 0) : -2, seg_p0 = read_lane(at_p0, 1);
   if (started_before) bad |= seg_before != s_f || seg_p0 != s_f;
   else bad |= seg_before == seg_p0 || seg_p0 != (p0 == A.o1 ? A.u + 1 : A.u);
   if (ballot(bad) && lane == 0) raise_err(a.dev_err, LM_DEVERR_CAPACITY);
   if (ballot(bad_row) && lane == 0) raise_err(a.dev_err, LM_DEVERR_ID_RANGE);
-  publish();
+
+  // 4. Fused: the pieces this wave wrote (at most two: of the segment it found
+  //    running, and of the one it left running).
+  if constexpr (FUSED) {
+    if (!(long_f || long_l)) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    bool flagged = false;
+    auto piece_done = [&](int s, int o0, int o1) {
+      const int cs = chunk_of(o0, s), P = chunk_of(o1 - 1, s) - cs;
+      if (P >= kHeadPieces) {
+        if (!flagged && lane == 0) word_add(word, a.tag, kPieceFlag);
+        flagged = true;  // both pieces may be of heads
+        return;
+      }
+      uint32_t n = 0;
+      if (lane == 0) n = word_add(a.flags + size_t(cs) * a.tiles + ct, a.tag, 1) & kCountMask;
+      if (first_lane(n) != P + 1) return;
+      // The last one: every piece is there.
+      constexpr int RP = NV * VEC >= 16 ? 4 : 8;  // pieces in flight
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[v][e] = 0.f;
+      for (int t0 = 0; t0 <= P; t0 += RP) {
+        float buf[RP][NV][VEC];
+#pragma unroll
+        for (int r = 0; r < RP; ++r)
+#pragma unroll
+          for (int v = 0; v < NV; ++v)
+            load_vec_agent<VEC, TAIL>(piece_row(a, cs, t0 + r <= P ? t0 + r : 0) + col_ld[v],
+                                      buf[r][v]);
+#pragma unroll
+        for (int r = 0; r < RP; ++r)
+          if (t0 + r <= P)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+              for (int e = 0; e < VEC; ++e) acc[v][e] += buf[r][v][e];
+      }
+      if (s >= a.u_cap) return;
+      const int64_t orow = out_row_of(a, s);
+      if (orow < 0) return;
+      float* dst = a.out + orow * a.ld_out;
+      if constexpr (OP != kOpStore) {
+        update_row(dst);
+      } else {
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+          if (col_ok[v]) store_vec<VEC>(dst + col_ld[v], acc[v]);
+      }
+    };
+    if (long_f) piece_done(s_f, A.o0, A.o1);
+    if (starts_long) piece_done(s_l, B.o0, B.o1);
+  }
 }
 
 // Sum the pieces of every long segment that spans chunks (piece 0 is
@@ -861,7 +1001,11 @@ __global__ __launch_bounds__(kFixThreads) void k_segsum_fix(SegArgs a) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) acc[e] += sbuf[r][e];
     const int64_t orow = out_row_of(a, ss);
-    if (col < D && orow >= 0) finish_row<VEC, OP>(a, orow, col, acc);
+    if (col < D && orow >= 0) {
+      TableVec<VEC, OP> tv;
+      tv.load(a, orow * a.ld_out + col);
+      tv.finish(a, orow * a.ld_out + col, acc);
+    }
   }
   if (ih < 0) return;  // the same in every wave: no barrier below is skipped by only some
   float acc[VEC];
@@ -896,7 +1040,9 @@ __global__ __launch_bounds__(kFixThreads) void k_segsum_fix(SegArgs a) {
       float sum = 0.f;
 #pragma unroll
       for (int w = 0; w < kFixWaves; ++w) sum += s_part[w][x];
-      finish_row<1, OP>(a, orow, cx, &sum);
+      TableVec<1, OP> tv;
+      tv.load(a, orow * a.ld_out + cx);
+      tv.finish(a, orow * a.ld_out + cx, &sum);
     }
   }
 }
@@ -957,21 +1103,21 @@ static void launch_one(SegArgs& a, int tiles, hipStream_t st) {
   // instantiations too: its occupancy fixes the chunks, and with them the
   // order of every sum, so lm_segsum_sgd and _adam add in lm_segsum's order.
   const bool fused = VEC >= 2 && a.fused;
-  const int64_t room = int64_t(plain_blocks<GT, VEC, NV, R, TAIL>(fused)) *
-                       (fused ? kFusedWaves : kSegWaves) * stream_cus(st);
-  a.nchunks = whole_rounds(a.nchunks, tiles, room, a.max_chunks);
+  const int64_t room =
+      int64_t(plain_blocks<GT, VEC, NV, R, TAIL>(fused)) * kSegWaves * stream_cus(st);
+  whole_rounds(a, room);
+  const int blocks = (a.nchunks + kSegWaves - 1) / kSegWaves;
   if constexpr (VEC >= 2) {
     if (fused) {
-      a.main_blocks = (a.nchunks + kFusedWaves - 1) / kFusedWaves * tiles;
-      const int fix_blocks = (a.nchunks + kFusedSpan - 1) / kFusedSpan * a.fix_tiles;
-      k_segsum<GT, VEC, NV, RF, R, T, kFusedThreads, true, OP, TAIL, EARLY>
-          <<<dim3(a.main_blocks + fix_blocks), kFusedThreads, 0, st>>>(a);
+      a.main_blocks = blocks * tiles;
+      const int fix_blocks = (a.nchunks - 1) / kHeadPieces * a.fix_tiles;
+      k_segsum<GT, VEC, NV, RF, R, T, true, OP, TAIL, EARLY>
+          <<<dim3(a.main_blocks + fix_blocks), kSegThreads, 0, st>>>(a);
       return;
     }
   }
-  const dim3 grid((a.nchunks + kSegWaves - 1) / kSegWaves, tiles);
-  k_segsum<GT, VEC, NV, RF, R, T, kSegThreads, false, OP, TAIL, EARLY>
-      <<<grid, kSegThreads, LMZ_SEG_LDS_PAD, st>>>(a);
+  k_segsum<GT, VEC, NV, RF, R, T, false, OP, TAIL, EARLY>
+      <<<dim3(blocks, tiles), kSegThreads, 0, st>>>(a);
 }
 
 // Whether an update loads the table rows of a batch's segment ends with the

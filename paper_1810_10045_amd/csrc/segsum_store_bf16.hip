@@ -15,15 +15,15 @@ int plain_blocks(bool fused) {
     hipError_t e;
     if constexpr (VEC >= 2) {
       e = fused ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                      &b, k_segsum<GT, VEC, NV, RF, R, T, kFusedThreads, true, kOpStore, TAIL, false>,
-                      kFusedThreads, 0)
+                      &b, k_segsum<GT, VEC, NV, RF, R, T, true, kOpStore, TAIL, false>,
+                      kSegThreads, 0)
                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                      &b, k_segsum<GT, VEC, NV, RF, R, T, kSegThreads, false, kOpStore, TAIL, false>,
-                      kSegThreads, LMZ_SEG_LDS_PAD);
+                      &b, k_segsum<GT, VEC, NV, RF, R, T, false, kOpStore, TAIL, false>,
+                      kSegThreads, 0);
     } else {
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &b, k_segsum<GT, VEC, NV, RF, R, T, kSegThreads, false, kOpStore, TAIL, false>, kSegThreads,
-          LMZ_SEG_LDS_PAD);
+          &b, k_segsum<GT, VEC, NV, RF, R, T, false, kOpStore, TAIL, false>, kSegThreads,
+          0);
     }
     if (e != hipSuccess) {
       (void)hipGetLastError();

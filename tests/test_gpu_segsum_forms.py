@@ -1,7 +1,6 @@
-"""Seg-Sum over rows whose width or start is no multiple of a 16-byte vector:
-the last lane's vector repeats columns of the lane before it, partial rows are
-exchanged column by column, and a last column tile narrower than a vector
-starts one vector earlier."""
+"""Seg-Sum's forms: rows whose width or start is no multiple of a 16-byte
+vector, updates whose table rows load early or late, and segments cut into any
+number of pieces."""
 import os
 import sys
 
@@ -116,3 +115,38 @@ def test_updates_on_either_side_of_the_early_rule(lz, K, V, D, gdt):
                     m=t2[1], v=t2[2], dev_err=r.dev_err)
     assert all(torch.equal(x, y) for x, y in zip(t1, t2))
     lz.check(r.dev_err)
+
+
+@pytest.mark.parametrize("length", [1, 7, 8, 16, 17, 31, 100, 255, 256, 257, 300, 1500, 6000])
+@pytest.mark.parametrize("D,gdt", [(512, "f32"), (1500, "f32"), (1100, "bf16")])
+def test_segments_of_one_length(lz, length, D, gdt):
+    """Types of `length` tokens each, over a list with room for far more types:
+    lengths around the shortest cut segment, one and several pieces, and the 16
+    further pieces from which a fix-up workgroup sums them; repeated calls on
+    one workspace agree, and so do the two launch forms within the tolerance."""
+    K, V = 6000, 100_000
+    print(f"segments of {length} D={D} {gdt}", flush=True)
+    base = np.repeat(np.arange((K + length - 1) // length) * 16 + 3, length)[:K].astype(np.int32)
+    ids = np.random.Generator(np.random.PCG64(length)).permutation(base)
+    g = torch.from_numpy(synth.normal_rows(K, D, 500 + length)).to(DEV)
+    g = g.to(torch.bfloat16) if gdt == "bf16" else g
+    ws = lz.Workspace(DEV)
+    r = lz.unique(torch.from_numpy(ids).to(DEV), V, ws=ws)
+    seg = (g, r.perm, r.inverse, r.offsets, r.num_unique)
+    one = [lz.segsum(*seg, dev_err=r.dev_err, ws=ws) for _ in range(3)]
+    assert lz.segsum_two_launches(True) is False
+    try:
+        two = lz.segsum(*seg, dev_err=r.dev_err, ws=ws)
+    finally:
+        assert lz.segsum_two_launches(False) is True
+    torch.cuda.synchronize()
+    lz.check(r.dev_err)
+    o = H.assert_unique_matches(r, ids, V, oracle)
+    U = len(o[0])
+    assert all(torch.equal(one[0][:U], x[:U]) for x in one[1:]), "not the same bits every time"
+    host = (g.view(torch.int16).cpu().numpy().view(np.uint16) if gdt == "bf16" else g.cpu().numpy())
+    ref = oracle.segsum(host, o[3], U)
+    for got in (one[0], two):
+        got = got[:U].double().cpu().numpy()
+        H.check_rows(got, ref, H.sum_of_squares(host, o[3], U, oracle), gdt)
+        H.assert_single_rows_exact(got, ref, o[1])
