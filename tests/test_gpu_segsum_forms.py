@@ -150,3 +150,21 @@ def test_segments_of_one_length(lz, length, D, gdt):
         got = got[:U].double().cpu().numpy()
         H.check_rows(got, ref, H.sum_of_squares(host, o[3], U, oracle), gdt)
         H.assert_single_rows_exact(got, ref, o[1])
+
+
+@pytest.mark.parametrize("K,V,D,gdt", [(16_385, 98, 200, "f32"), (21_386, 2865, 357, "f32"),
+                                       (60_000, 500, 358, "f32"), (40_000, 2000, 300, "bf16")])
+def test_sums_where_chunks_are_made_to_fill_the_device(lz, K, V, D, gdt):
+    """Chunk counts raised to a number of waves: whole and part vectors, chunks
+    down to 16 rows, heads and short cut segments. Rows of small whole numbers,
+    whose sums are exact in fp32 in any order."""
+    print(f"filled K={K} V={V} D={D} {gdt}", flush=True)
+    ids = torch.from_numpy(synth.zipf_ids(K, V, 1.1, 700 + K, np.int32)).to(DEV)
+    grad = torch.from_numpy(np.random.Generator(np.random.PCG64(K)).integers(-8, 9, (K, D))).to(DEV)
+    want = torch.zeros((V, D), dtype=torch.int64, device=DEV).index_add_(0, ids.long(), grad)
+    grad = grad.to(torch.bfloat16 if gdt == "bf16" else torch.float32)
+    r = lz.unique(ids, V)
+    out = lz.segsum(grad, r.perm, r.inverse, r.offsets, r.num_unique, dev_err=r.dev_err)
+    lz.check(r.dev_err)
+    U = int(r.num_unique.item())
+    assert torch.equal(out[:U].double(), want[r.uniq[:U].long()].double())
