@@ -55,6 +55,7 @@
 #include <atomic>
 
 #include "segsum_args.hpp"
+#include "segsum_words.hpp"
 
 namespace lmz {
 
@@ -233,7 +234,7 @@ __device__ __forceinline__ void chunk_bounds(const int (&s_win)[N + 1], int lo, 
 // the walk waits for them before it says so in a word per chunk and column
 // tile, and they are read with agent-scope loads. A word holds a tag that is
 // new for every call (of a per-process counter) above its count and flag, so
-// no workspace contents need clearing between calls (word_add).
+// no workspace contents need clearing between calls (segsum_words.hpp).
 //   A segment of fewer than kHeadPieces further pieces: the wave that adds the
 //   last of its pieces to the count in the word of the segment's first chunk
 //   sums them all, in order. No wave waits for another.
@@ -258,28 +259,14 @@ __device__ __forceinline__ void chunk_bounds(const int (&s_win)[N + 1], int lo, 
 #define LMZ_SEG_FUSED_SLEEP 8        // s_sleep argument (x 64 cycles) between flag polls
 #endif
 constexpr int kHeadPieces = 16;  // further pieces from which a segment is a head
-// A chunk's word: the tag, a flag and a count.
-constexpr int kTagShift = 20;
-constexpr uint64_t kPieceFlag = 1u << 19;
-constexpr uint32_t kCountMask = (1u << 19) - 1;
-
-// Add to a chunk's word, which may still hold what an earlier call (or other
-// data) left: returns its flag and count after the addition.
-__device__ __forceinline__ uint32_t word_add(uint64_t* w, uint64_t tag, uint64_t x) {
-  constexpr uint64_t kLow = (1u << kTagShift) - 1;
-  uint64_t old = add_agent(w, x);
-  while ((old >> kTagShift) != tag) {  // ends: a failed exchange is another's success
-    uint64_t cur = ld_agent(w);
-    if ((cur >> kTagShift) == tag) {
-      old = add_agent(w, x);
-    } else if (__hip_atomic_compare_exchange_strong(w, &cur, (tag << kTagShift) | x,
-                                                    __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT)) {
-      return static_cast<uint32_t>(x);
-    }
+// The memory operations of the words (segsum_words.hpp).
+struct AgentWords {
+  __device__ __forceinline__ void exchange_if(uint64_t* w, uint64_t seen, uint64_t x) const {
+    __hip_atomic_compare_exchange_strong(w, &seen, x, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
   }
-  return static_cast<uint32_t>((old & kLow) + x);
-}
+  __device__ __forceinline__ uint64_t add(uint64_t* w, uint64_t x) const { return add_agent(w, x); }
+};
 
 // The output row of type s: s itself, or row_ids[s] for lm_segsum_rows
 // (-1 when that id lies outside [0, out_rows); LM_DEVERR_ID_RANGE is raised
@@ -411,7 +398,7 @@ constexpr int ends_for() {
 __device__ __forceinline__ bool wait_piece(const SegArgs& a, int x, int ct, bool need) {
   for (uint32_t spin = 0;; ++spin) {
     const uint64_t f = need ? ld_agent(a.flags + size_t(x) * a.tiles + ct) : 0;
-    const bool ok = !need || ((f >> kTagShift) == a.wait_tag && (f & kPieceFlag));
+    const bool ok = !need || (word_is(f, a.wait_tag) && (f & kPieceFlag));
     if (!ballot(!ok)) return true;
     if (spin >= a.spin_limit) {
       if (lane_id() == 0) raise_err(a.dev_err, LM_DEVERR_SPIN);
@@ -612,12 +599,21 @@ __global__ __launch_bounds__(kSegThreads) void k_segsum(SegArgs a) {
     pos = pos < q_end ? pos : q_end;
     pw[w] = a.perm[pos < 0 ? 0 : (pos < K ? pos : K - 1)];
   }
-  //    The chunk's word too, so that its tag is this call's by the time a piece
-  //    is done.
-  uint64_t* const word = a.flags + size_t(c) * a.tiles + ct;
-  uint64_t word0 = 0;
+  //    The words this wave will add to, to claim them before a piece is done:
+  //    its own chunk's (lane 0) and, where a segment of few pieces began
+  //    before, that of the chunk it began in (lane 1).
+  int cs_f = 0, P_f = 0;
+  uint64_t* word = nullptr;
+  uint64_t seen = 0;
+  bool claims = false;
   if constexpr (FUSED) {
-    if ((long_f || long_l) && lane == 0) word0 = ld_agent(word);
+    if (long_f) {
+      cs_f = chunk_of(A.o0, s_f);
+      P_f = chunk_of(A.o1 - 1, s_f) - cs_f;
+    }
+    word = a.flags + size_t(lane == 1 ? cs_f : c) * a.tiles + ct;
+    claims = lane == 0 ? long_f || long_l : lane == 1 && long_f && P_f < kHeadPieces;
+    if (claims) seen = ld_agent(word);
   }
   //    While it flies: ends[w] bit j: position p0-1+64w+j is the last of its
   //    segment, from the offsets in LDS (type A.u + i ends before
@@ -656,9 +652,7 @@ __global__ __launch_bounds__(kSegThreads) void k_segsum(SegArgs a) {
     }
   }
   if constexpr (FUSED) {
-    if ((long_f || long_l) && lane == 0 && (word0 >> kTagShift) != a.tag)
-      __hip_atomic_compare_exchange_strong(word, &word0, a.tag << kTagShift, __ATOMIC_RELAXED,
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (claims) word_claim(AgentWords{}, word, seen, a.tag);
   }
   // The map of the tokens either side of p0 (the arrays' consistency, below).
   const int at_p0 = a.inverse[lane == 0 ? read_lane(pw[0], 0) : read_lane(pw[0], 1)];
@@ -862,20 +856,23 @@ __global__ __launch_bounds__(kSegThreads) void k_segsum(SegArgs a) {
   if (ballot(bad_row) && lane == 0) raise_err(a.dev_err, LM_DEVERR_ID_RANGE);
 
   // 4. Fused: the pieces this wave wrote (at most two: of the segment it found
-  //    running, and of the one it left running).
+  //    running, and of the one it left running). The wait also orders the
+  //    claims (lane 1's too) before the additions.
   if constexpr (FUSED) {
     if (!(long_f || long_l)) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    uint64_t* const first_word = a.flags + ct;
     bool flagged = false;
-    auto piece_done = [&](int s, int o0, int o1) {
-      const int cs = chunk_of(o0, s), P = chunk_of(o1 - 1, s) - cs;
+    auto piece_done = [&](int s, int cs, int P) {
       if (P >= kHeadPieces) {
-        if (!flagged && lane == 0) word_add(word, a.tag, kPieceFlag);
+        if (!flagged && lane == 0)
+          word_add(AgentWords{}, first_word + size_t(c) * a.tiles, kPieceFlag);
         flagged = true;  // both pieces may be of heads
         return;
       }
       uint32_t n = 0;
-      if (lane == 0) n = word_add(a.flags + size_t(cs) * a.tiles + ct, a.tag, 1) & kCountMask;
+      if (lane == 0)
+        n = word_count(word_add(AgentWords{}, first_word + size_t(cs) * a.tiles, 1));
       if (first_lane(n) != P + 1) return;
       // The last one: every piece is there.
       constexpr int RP = NV * VEC >= 16 ? 4 : 8;  // pieces in flight
@@ -911,8 +908,8 @@ __global__ __launch_bounds__(kSegThreads) void k_segsum(SegArgs a) {
           if (col_ok[v]) store_vec<VEC>(dst + col_ld[v], acc[v]);
       }
     };
-    if (long_f) piece_done(s_f, A.o0, A.o1);
-    if (starts_long) piece_done(s_l, B.o0, B.o1);
+    if (long_f) piece_done(s_f, cs_f, P_f);
+    if (starts_long) piece_done(s_l, c, chunk_of(B.o1 - 1, s_l) - c);
   }
 }
 
