@@ -104,58 +104,6 @@ int stream_cus(hipStream_t st) {
   return c > 0 && c < n ? c : n;
 }
 
-// Whole rounds of waves. The walk's waves (chunks x column tiles) of equal
-// cost run in rounds of as many waves as fit at once on the compute units
-// the launch's stream may use. Where a
-// last round would be less than half full, its few waves run nearly alone,
-// far below the memory system's rate: the chunk count then grows (so the
-// chunks shrink) until the last round is full, at most to the workspace's
-// capacity (a chunk count above the minimum only shortens chunks).
-// Measured at K = 1,048,576, D = 2048 fp32 (two column tiles, room for
-// 2,048 waves): 2,088 chunks (4,176 waves) 1,591 us, 3,072 chunks 1,488 us.
-// Where the last round was half full or more (the bf16 merge: 10,347 waves
-// on room for 4,096) rounding up changed nothing measurable.
-// Less than one round is filled up too where chunks are long (R >= 256): a
-// wave waits for each batch of its rows, so half as many waves leave the memory
-// half idle. Measured, fp32: 524,288 ids over 20K words, D = 512 (1,063 waves
-// on room for 2,048) 286 -> 208 us, 200,000 over 20K, D = 256 60 -> 52 us,
-// 262,144 over 2M, D = 1024 (2,048 on 4,096) 339 -> 336 us.
-// Shorter chunks (R = 32 .. 128) make kWaves waves, two workgroups on each
-// compute unit, where there would be well below that many and none gets fewer
-// than kMinR rows, and no more than
-// kEnoughWaves unless a chunk would exceed R, as every cut may cost a partial
-// row. Measured, waves before -> now: Adam, D = 1792, 19,200 ids over 98 43.2
-// us (1,208) -> 39.7 (1,536 waves 41.6, 2,560 43.8); D = 300, 40,000 over 2,000
-// 40.4 (627) -> 25.2; SGD, D = 512, 106,496 over 800K 71.7 (1,664) -> 67.5;
-// bf16, D = 1792, 19,200 over 15,437 38.0 (5,058) -> 33.6 (2,560). Close to
-// kWaves it loses: 30,011 over 50K, D = 650 38.3 (1,876) -> 40.5. So does it
-// with chunks of 10 rows: 20,000 over 98, D = 200 17.2 us (2,048), 13.6 (1,280).
-// Rows that are no whole number of vectors write their partial rows a column
-// at a time: half as many waves. 21,386 over 2,865, D = 358: 22.2 us (2,048),
-// 17.7 (1,024), 18.9 (669 as they come); 60,000 over 500, D = 358 45.0, 32.1,
-// 32.2; SGD, 100,000 over 1,000, D = 513 59.6, 51.9, 55.3.
-constexpr int kWaves = 2048, kTailWaves = kWaves / 2, kEnoughWaves = 2560;
-void whole_rounds(SegArgs& a, int64_t waves_per_round) {
-  a.enough = a.nchunks;
-  if (waves_per_round <= 0 || a.tiles <= 0) return;
-  const int64_t waves = int64_t(a.nchunks) * a.tiles;
-  const int64_t last = waves % waves_per_round;
-  const bool tail = a.D % (16 / (a.rw / 2)) != 0;  // rw: twice a column's bytes
-  const int fill = tail ? kTailWaves : kWaves;
-  int64_t want = a.nchunks;
-  if (a.R >= 256 ? last != 0 && (waves < waves_per_round || 2 * last < waves_per_round)
-                 : waves > waves_per_round && last != 0 && 2 * last < waves_per_round) {
-    const int64_t rounds = (waves + waves_per_round - 1) / waves_per_round;
-    want = (rounds * waves_per_round + a.tiles - 1) / a.tiles;
-  } else if (a.R > kMinR && a.R < 256 && waves < fill - fill / 8) {
-    want = (fill + a.tiles - 1) / a.tiles;
-    if (want > a.K / kMinR) want = a.K / kMinR;
-  }
-  if (want > a.max_chunks) want = a.max_chunks;
-  if (want > a.nchunks) a.nchunks = static_cast<int>(want);
-  a.enough = a.R < 256 ? (kEnoughWaves + a.tiles - 1) / a.tiles : a.nchunks;
-}
-
 template <int OP>
 static hipError_t run_op(SegArgs& a, int gtype, hipStream_t st) {
   const hipError_t e =

@@ -4,10 +4,10 @@
 #pragma once
 
 #include "common.hpp"
+#include "segsum_plan.hpp"
 
 namespace lmz {
 
-constexpr int kMinR = 16, kMaxR = 512;  // shortest and longest chunks
 constexpr int kFusedCols = kWave * 4;   // columns of a fused fix-up tile
 
 struct SegArgs {
@@ -57,9 +57,7 @@ hipError_t seg_walk(SegArgs& a, hipStream_t st);
 template <int OP>
 void seg_fix(const SegArgs& a, hipStream_t st);
 
-// Compute units a launch on `st` may use, and the chunk counts for the waves
-// that fit on them at once (segsum.hip).
+// Compute units a launch on `st` may use (segsum.hip).
 int stream_cus(hipStream_t st);
-void whole_rounds(SegArgs& a, int64_t waves_per_round);
 
 }  // namespace lmz

@@ -1100,9 +1100,13 @@ static void launch_one(SegArgs& a, int tiles, hipStream_t st) {
   // instantiations too: its occupancy fixes the chunks, and with them the
   // order of every sum, so lm_segsum_sgd and _adam add in lm_segsum's order.
   const bool fused = VEC >= 2 && a.fused;
-  const int64_t room =
-      int64_t(plain_blocks<GT, VEC, NV, R, TAIL>(fused)) * kSegWaves * stream_cus(st);
-  whole_rounds(a, room);
+  const int cus = stream_cus(st);
+  const int64_t room = int64_t(plain_blocks<GT, VEC, NV, R, TAIL>(fused)) * kSegWaves * cus;
+  const bool part_vec = a.D % (16 / static_cast<int>(sizeof(GT))) != 0;
+  const ChunkCount cc =
+      whole_rounds(a.K, R, part_vec, tiles, a.nchunks, a.max_chunks, room, cus);
+  a.nchunks = cc.n;
+  a.enough = cc.enough;
   const int blocks = (a.nchunks + kSegWaves - 1) / kSegWaves;
   if constexpr (VEC >= 2) {
     if (fused) {
