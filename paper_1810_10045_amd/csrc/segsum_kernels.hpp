@@ -98,6 +98,7 @@ namespace lmz {
 #endif
 constexpr int kSegThreads = 256;     // threads of a workgroup: a chunk per wave
 constexpr int kSegWaves = kSegThreads / kWave;
+static_assert(kSegWaves == kGroupWaves, "the chunk counts assume it");
 
 // Windows of positions a wave loads up front: [p0 - 1, p0 - 1 + 64 * NW)
 // must cover p0 - 1 (to see whether the first segment started earlier), the
@@ -1103,8 +1104,8 @@ static void launch_one(SegArgs& a, int tiles, hipStream_t st) {
   const int cus = stream_cus(st);
   const int64_t room = int64_t(plain_blocks<GT, VEC, NV, R, TAIL>(fused)) * kSegWaves * cus;
   const bool part_vec = a.D % (16 / static_cast<int>(sizeof(GT))) != 0;
-  const ChunkCount cc =
-      whole_rounds(a.K, R, part_vec, tiles, a.nchunks, a.max_chunks, room, cus);
+  const ChunkCount cc = whole_rounds(a.K, a.u_cap, R, sizeof(GT) == 2, part_vec, tiles, a.nchunks,
+                                     a.max_chunks, room, cus);
   a.nchunks = cc.n;
   a.enough = cc.enough;
   const int blocks = (a.nchunks + kSegWaves - 1) / kSegWaves;
@@ -1144,12 +1145,10 @@ template <typename GT, int OP, int R>
 constexpr bool may_be_early() {
   return OP == kOpSgd && sizeof(GT) == 4 && R < LMZ_SEG_LONG_R;
 }
-constexpr int kEarlyTokensPerType = 32;
-
 template <typename GT, int VEC, int NV, int R, int OP, bool TAIL>
 static void launch_when(SegArgs& a, int tiles, hipStream_t st) {
   if constexpr (may_be_early<GT, OP, R>()) {
-    if (a.K < kEarlyTokensPerType * a.u_cap) {
+    if (a.K < kFewTokens * a.u_cap) {
       launch_one<GT, VEC, NV, R, OP, TAIL, true>(a, tiles, st);
       return;
     }

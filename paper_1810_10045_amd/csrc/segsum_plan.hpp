@@ -25,47 +25,76 @@ struct ChunkCount {
 // 2,048 waves): 2,088 chunks (4,176 waves) 1,591 us, 3,072 chunks 1,488 us.
 // Where the last round was half full or more (the bf16 merge: 10,347 waves
 // on room for 4,096) rounding up changed nothing measurable.
-// Less than one round is filled up too where chunks are long (R >= 256): a
-// wave waits for each batch of its rows, so half as many waves leave the memory
-// half idle. Measured, fp32: 524,288 ids over 20K words, D = 512 (1,063 waves
-// on room for 2,048) 286 -> 208 us, 200,000 over 20K, D = 256 60 -> 52 us,
-// 262,144 over 2M, D = 1024 (2,048 on 4,096) 339 -> 336 us.
-// Shorter chunks (R = 32 .. 128) make kFillWaves waves for each compute unit,
-// two workgroups, where there would be well below that many and chunks hold no
-// fewer than kMinR positions on average, and no more than kEnoughWaves for each
-// unless a chunk would exceed R, as every cut may cost a partial
-// row. Measured on 256 compute units, waves before -> now: Adam, D = 1792,
-// 19,200 ids over 98 43.2 us (1,208) -> 39.7 (1,536 waves 41.6, 2,560 43.8);
-// D = 300, 40,000 over 2,000 40.4 (627) -> 25.2; SGD, D = 512, 106,496 over
-// 800K 71.7 (1,664) -> 67.5; bf16, D = 1792, 19,200 over 15,437 38.0 (5,058)
-// -> 33.6 (2,560). Close to kFillWaves it loses: 30,011 over 50K, D = 650 38.3
-// (1,876) -> 40.5. So does it with chunks of 10 rows: 20,000 over 98, D = 200
-// 17.2 us (2,048), 13.6 (1,280).
-// Rows that are no whole number of vectors (part_vec) write their partial rows
-// a column at a time: half as many waves. 21,386 over 2,865, D = 358: 22.2 us
-// (2,048), 17.7 (1,024), 18.9 (669 as they come); 60,000 over 500, D = 358
-// 45.0, 32.1, 32.2; SGD, 100,000 over 1,000, D = 513 59.6, 51.9, 55.3.
+//
+// Less than one round, many types (fewer than kFewTokens positions for each
+// type there may be). A wave waits for each batch of its rows and for what its
+// segment ends need, so too few waves leave the memory half idle.
+//   Long chunks (R >= 256) fill the round. Measured on 256 compute units, fp32:
+//   524,288 ids over 20K words, D = 512 (1,063 waves on room for 2,048) 286 ->
+//   208 us, 200,000 over 20K, D = 256 60 -> 52 us; bf16, 400,000 over 300K,
+//   D = 512 (3,125 on 4,096) 132 -> 118.
+//   Shorter ones (R = 32 .. 128) make kFillWaves waves for each compute unit,
+//   two workgroups, where there would be well below that many and chunks hold
+//   no fewer than kMinR positions on average. Waves before -> now: D = 300,
+//   40,000 over 2,000, Adam 32 us (627) -> 23; SGD, D = 512, 106,496 over 800K
+//   77 (1,664) -> 73. Close to kFillWaves it loses: 30,011 over 50K, D = 650
+//   38.3 (1,876) -> 40.5. So does it with chunks of 10 rows: 20,000 over 98,
+//   D = 200 17.2 us (2,048), 13.6 (1,280).
+//   Rows that are no whole number of vectors (part_vec) write their partial
+//   rows a column at a time: half as many waves. 21,386 over 2,865, D = 358:
+//   22.2 us (2,048), 17.7 (1,024), 18.9 (669 as they come).
+//
+// Less than one round, few types: nearly every cut goes through a long segment
+// and costs a partial row, and a head's pieces are summed one after the other.
+// So only whole workgroups for each compute unit are filled up: one where
+// chunks keep kFewRows positions, or two where one and a part are needed
+// anyway (not with part_vec). us as they come / here / as with many types:
+//   bf16, 30,000 ids over 98 characters, D = 1024 (950 waves) 22.7 / 22.7 /
+//     31.2; D = 352, 905,469 over 221 (1,769) 124 / 118 (2,048) / 128;
+//     D = 512, 100,000 over 500 (786) 32.9 / 29.1 (1,024) / 31.3;
+//   fp32, 60,000 over 500, D = 1024 (945) 49.2 / 49.2 / 53.7; 262,144 over 98,
+//     D = 1024 (1,025) 174 / 174 / 200; 200,000 over 98, D = 256 (782) 53 / 40
+//     (1,024) / 55; Adam, 19,200 over 98, D = 1792 (1,208) 43.0 / 39.7 (2,048)
+//     / 39.7; D = 512 (604) 17.0 / 17.0 / 17.7.
+//
+// kEnoughWaves for each compute unit are enough with bf16 rows where far fewer
+// types turn up than there is room for, unless a chunk would exceed R: room for
+// types is counted at four positions each there, so chunks get as short as R / 5,
+// and every cut may cost a partial row of twice a row's bytes. 30,011 over 50K,
+// D = 1792 (9,380 waves) 55.4 -> 46.7 us (2,560). With fp32 rows chunks keep
+// R / 2, and fewer lose their whole rounds: 120,000 over 800K, D = 1500 210 ->
+// 220 us, 65,536 over 800K, D = 2048 136 -> 139.
 constexpr int kFillWaves = 8, kEnoughWaves = 10;  // for each compute unit
+constexpr int kGroupWaves = 4;                    // waves of a workgroup
+constexpr int kFewTokens = 32, kFewRows = 64;
 
-inline ChunkCount whole_rounds(int64_t K, int R, bool part_vec, int tiles, int nchunks,
-                               int max_chunks, int64_t waves_per_round, int cus) {
+inline ChunkCount whole_rounds(int64_t K, int64_t u_cap, int R, bool bf16, bool part_vec, int tiles,
+                               int nchunks, int max_chunks, int64_t waves_per_round, int cus) {
   ChunkCount c{nchunks, nchunks};
   if (waves_per_round <= 0 || tiles <= 0 || cus <= 0) return c;
   const int64_t waves = int64_t(nchunks) * tiles;
-  const int64_t last = waves % waves_per_round;
-  const int64_t fill = int64_t(cus) * (part_vec ? kFillWaves / 2 : kFillWaves);
-  int64_t want = nchunks;
-  if (R >= 256 ? last != 0 && (waves < waves_per_round || 2 * last < waves_per_round)
-               : waves > waves_per_round && last != 0 && 2 * last < waves_per_round) {
-    const int64_t rounds = (waves + waves_per_round - 1) / waves_per_round;
-    want = (rounds * waves_per_round + tiles - 1) / tiles;
-  } else if (R > kMinR && R < 256 && waves < fill - fill / 8) {
-    want = (fill + tiles - 1) / tiles;
-    if (want > K / kMinR) want = K / kMinR;
+  int64_t fill = waves, most = max_chunks;  // waves to make, chunks at most
+  if (waves > waves_per_round) {
+    const int64_t last = waves % waves_per_round;
+    if (last != 0 && 2 * last < waves_per_round) fill = waves - last + waves_per_round;
+  } else if (K >= kFewTokens * u_cap) {
+    const int64_t group = int64_t(cus) * kGroupWaves;
+    const bool two = waves > group + group / 8;
+    const int64_t want = R == kMinR || (two && part_vec) ? 0 : two ? 2 * group : group;
+    if (waves < want - want / 8 && K / (two ? kMinR : kFewRows) >= (want + tiles - 1) / tiles)
+      fill = want;
+  } else if (R >= 256) {
+    fill = waves_per_round;
+  } else if (R > kMinR) {
+    const int64_t want = int64_t(cus) * (part_vec ? kFillWaves / 2 : kFillWaves);
+    if (waves < want - want / 8) fill = want;
+    if (most > K / kMinR) most = K / kMinR;
   }
-  if (want > max_chunks) want = max_chunks;
+  int64_t want = (fill + tiles - 1) / tiles;
+  if (want > most) want = most;
   if (want > nchunks) c.n = static_cast<int>(want);
-  c.enough = R < 256 ? static_cast<int>((int64_t(cus) * kEnoughWaves + tiles - 1) / tiles) : c.n;
+  c.enough = c.n;
+  if (bf16 && R < 256) c.enough = static_cast<int>((int64_t(cus) * kEnoughWaves + tiles - 1) / tiles);
   return c;
 }
 

@@ -1,5 +1,6 @@
 """How many chunks Seg-Sum cuts a call into (csrc/segsum_plan.hpp), compiled for
-the host: the counts follow the compute units that the call's stream may use."""
+the host: the counts follow the compute units that the call's stream may use,
+and calls with few types are not cut for more waves than those can start at once."""
 import ctypes
 import os
 import subprocess
@@ -11,10 +12,10 @@ CSRC = os.path.join(ROOT, "paper_1810_10045_amd", "csrc")
 
 SOURCE = r"""
 #include "segsum_plan.hpp"
-extern "C" void rounds(int64_t K, int R, int part_vec, int tiles, int nchunks, int max_chunks,
-                       int64_t room, int cus, int* n, int* enough) {
-  const lmz::ChunkCount c =
-      lmz::whole_rounds(K, R, part_vec != 0, tiles, nchunks, max_chunks, room, cus);
+extern "C" void rounds(int64_t K, int64_t u_cap, int R, int bf16, int part_vec, int tiles,
+                       int nchunks, int max_chunks, int64_t room, int cus, int* n, int* enough) {
+  const lmz::ChunkCount c = lmz::whole_rounds(K, u_cap, R, bf16 != 0, part_vec != 0, tiles, nchunks,
+                                              max_chunks, room, cus);
   *n = c.n;
   *enough = c.enough;
 }
@@ -29,47 +30,69 @@ def plan(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I", CSRC, "-o", so,
                     str(d / "plan.cpp")], check=True)
     f = ctypes.CDLL(so).rounds
-    f.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 5 + [ctypes.c_int64, ctypes.c_int,
-                                                          ctypes.c_void_p, ctypes.c_void_p]
+    f.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int] * 6 + [ctypes.c_int64, ctypes.c_int,
+                                                             ctypes.c_void_p, ctypes.c_void_p]
 
-    def rounds(K, R, part_vec, tiles, nchunks, max_chunks, blocks, cus):
-        """`blocks` workgroups of 4 waves fit on a compute unit."""
+    def rounds(K, u_cap, R, need, tiles=1, bf16=0, part=0, blocks=4, cus=256, most=None):
+        """`need` chunks; `blocks` workgroups of 4 waves fit on a compute unit."""
         n, enough = ctypes.c_int(), ctypes.c_int()
-        f(K, R, part_vec, tiles, nchunks, max_chunks, 4 * blocks * cus, cus, ctypes.byref(n),
-          ctypes.byref(enough))
+        f(K, min(K, u_cap), R, bf16, part, tiles, need, most or 5 * K // R + 1, 4 * blocks * cus,
+          cus, ctypes.byref(n), ctypes.byref(enough))
         return n.value, enough.value
     return rounds
 
 
-# fp32 calls on 256 compute units: (K, R, part vector, tiles, chunks needed) -> chunks
-@pytest.mark.parametrize("K,R,part,tiles,need,want", [
-    (19_200, 32, 0, 2, 604, 1024), (40_000, 64, 0, 1, 627, 2048), (106_496, 128, 0, 1, 1664, 2048),
-    (30_011, 32, 0, 1, 1876, 1876), (20_000, 32, 0, 1, 629, 1250), (60_000, 64, 1, 1, 946, 946),
-    (21_386, 32, 1, 1, 669, 1024), (640, 16, 0, 1, 63, 63)])
-def test_short_chunks_fill_the_device(plan, K, R, part, tiles, need, want):
-    assert plan(K, R, part, tiles, need, 5 * K // R + 1, 4, 256) == \
-        (want, need if R >= 256 else -(-2560 // tiles))
+# Calls on 256 compute units: chunks needed (one round at most) -> chunks.
+MANY = [(40_000, 2_000, 64, 627, 2048, {}), (106_496, 800_000, 128, 1664, 2048, {}),
+        (30_011, 50_000, 32, 1876, 1876, {}), (21_386, 2_865, 32, 669, 1024, dict(part=1)),
+        (20_000, 5_000, 32, 629, 1250, {}), (640, 10_000, 16, 63, 63, {}),
+        (100_000, 5_000, 128, 938, 2048, dict(bf16=1)),
+        (524_288, 20_000, 512, 1063, 2048, dict(blocks=2)),
+        (200_000, 20_000, 256, 860, 3907, dict(blocks=6))]  # the workspace's room
+FEW = [(30_000, 98, 32, 950, 950, dict(bf16=1)), (60_000, 500, 64, 945, 945, {}),
+       (100_000, 500, 128, 786, 1024, dict(bf16=1)), (19_200, 98, 32, 604, 604, {}),
+       (19_200, 98, 32, 604, 1024, dict(tiles=2)), (19_200, 98, 32, 604, 604, dict(tiles=2, part=1)),
+       (200_000, 98, 256, 782, 1024, dict(blocks=6)), (262_144, 98, 256, 1025, 1025, {}),
+       (905_469, 221, 512, 1769, 2048, dict(bf16=1)),
+       (16_000, 98, 16, 900, 900, {})]
+
+
+@pytest.mark.parametrize("K,V,R,need,want,how", MANY + FEW)
+def test_less_than_one_round(plan, K, V, R, need, want, how):
+    """Long segments are cut for whole workgroups of the compute units only."""
+    assert (K >= 32 * V) == ((K, V, R, need, want, how) in FEW)
+    assert plan(K, V, R, need, **how)[0] == want
 
 
 @pytest.mark.parametrize("cus", [32, 64, 128, 224, 256])
 @pytest.mark.parametrize("part", [0, 1])
-def test_waves_follow_the_compute_units_of_the_stream(plan, cus, part):
+@pytest.mark.parametrize("V", [100, 4000])
+def test_waves_follow_the_compute_units_of_the_stream(plan, cus, part, V):
     """Never filled above 8 waves (4 where partial rows are written a column at
     a time) for each compute unit of the stream; as many as are needed stay."""
-    K, R = 40_000, 64
-    top = cus * (4 if part else 8)
-    for need in (16, top // 2, top - top // 8 - 1, top - top // 8, top, 3 * top // 2):
-        n, enough = plan(K, R, part, 1, need, 5 * K // R + 1, 4, cus)
-        assert n == (min(top, K // 16) if need < top - top // 8 else need), need
-        assert enough == 10 * cus
+    K, R = 100_000, 64
+    for need in (16, cus, 3 * cus, 4 * cus, 5 * cus, 7 * cus, 8 * cus, 12 * cus):
+        n, enough = plan(K, V, R, need, part=part, cus=cus)
+        assert need <= n <= max(need, cus * (4 if part else 8)) and enough == n
+        assert n in (need, 4 * cus, 8 * cus)
+        assert plan(K, V, R, need, part=part, cus=cus, bf16=1) == (n, 10 * cus)
 
 
-def test_long_chunks_fill_whole_rounds(plan):
-    assert plan(524_288, 512, 0, 1, 1063, 5121, 2, 256)[0] == 2048
-    assert plan(524_288, 512, 0, 1, 1063, 5121, 2, 32)[0] == 1280  # a last round 39 of 256 full
-    assert plan(1_048_576, 512, 0, 2, 2088, 10241, 2, 256)[0] == 3072
+def test_whole_rounds(plan):
+    assert plan(1_048_576, 98, 512, 2088, tiles=2, blocks=2)[0] == 3072
+    assert plan(1_048_576, 98, 512, 2049, blocks=2)[0] == 4096
+    assert plan(524_288, 20_000, 512, 1063, blocks=2, cus=32)[0] == 1280  # 39 of 256 in the last
+    assert plan(524_288, 20_000, 512, 1200, blocks=2, cus=32)[0] == 1200  # 176 of 256
+    assert plan(524_288, 20_000, 512, 1063, blocks=2, cus=32, most=1100)[0] == 1100
+
+
+def test_the_chunk_length_stays_with_fp32_rows(plan):
+    """Only bf16 calls lower the count where few types turn up."""
+    assert plan(120_000, 800_000, 128, 1875, tiles=2) == (1875, 1875)
+    assert plan(30_011, 50_000, 32, 4690, tiles=2, bf16=1)[1] == 1280
+    assert plan(400_000, 300_000, 512, 3125, bf16=1) == (3907, 3907)  # the workspace's room
 
 
 def test_an_unknown_device_keeps_the_chunks_it_needs(plan):
-    assert plan(40_000, 64, 0, 1, 627, 3126, 0, 256)[0] == 627
-    assert plan(40_000, 64, 0, 1, 627, 3126, 4, 0)[0] == 627
+    assert plan(40_000, 2_000, 64, 627, blocks=0) == (627, 627)
+    assert plan(40_000, 2_000, 64, 627, cus=0) == (627, 627)
