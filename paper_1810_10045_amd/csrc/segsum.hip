@@ -187,13 +187,12 @@ int segsum_run(const void* grad, int gtype, int64_t K, int64_t D, int64_t ld_gra
   a.m = m;
   a.v = v;
 
-  // One launch for the walk and the fix-up on the vector path (rows of at
-  // least one 16-byte vector, at any alignment). Measured at
+  // One launch for the walk and the fix-up on the vector path. Measured at
   // K = 1,048,576, D = 2048 fp32 (two column tiles): 1,490 us as the walk
   // and a separate fix-up kernel, 1,411 us in one launch, the fix-up
   // workgroups running in the walk's last round.
-  a.fused = LMZ_SEG_FUSED != 0 && D >= (gtype == LM_F32 ? 4 : 8) && D <= LMZ_SEG_FUSED_MAX_D &&
-            !two_launches();
+  a.by_column = column_per_lane(reinterpret_cast<uintptr_t>(grad), ld_grad, D, gtype == LM_BF16);
+  a.fused = LMZ_SEG_FUSED != 0 && !a.by_column && D <= LMZ_SEG_FUSED_MAX_D && !two_launches();
   // A captured launch would replay with this call's tag every time, and a
   // replay could take the previous replay's pieces for its own: under stream
   // capture the fix-up is a second launch, which keeps no state across calls.

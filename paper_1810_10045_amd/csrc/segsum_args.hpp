@@ -31,6 +31,7 @@ struct SegArgs {
                       // hook, one no walk writes)
   uint32_t spin_limit;  // polls of a flag before the wait gives up
   int main_blocks, fix_tiles, fused;
+  int by_column;           // the walk reads a column per lane (column_per_lane)
   int tiles, tile_cols;    // column tiles of the walk and the columns of one
   int thin;                // TAIL kernels: columns by which the last tile starts earlier
   int R, nchunks, rw, ww;  // cost of a position / of a segment end

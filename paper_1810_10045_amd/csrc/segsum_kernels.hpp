@@ -1172,12 +1172,12 @@ static hipError_t launch_r(SegArgs& a, hipStream_t st) {
 }
 
 // 16-byte vectors wherever a row holds one (4 fp32 or 8 bf16 columns), at any
-// alignment, up to 1024 columns of a row per wave; narrower rows take a column
-// per lane. A column per lane had been the path of every row that is no whole
-// number of aligned vectors: four times the load instructions for the same
-// bytes, and a second launch for the fix-up. Measured with SGD at 30,011 ids
-// over 50K words, D = 650 fp32: walk and fix-up 37.3 + 7.6 us before, 40.1 us
-// in one launch now.
+// alignment, up to 1024 columns of a row per wave; other rows, and bf16 rows
+// that column_per_lane names, take a column per lane. A column per lane had
+// been the path of every row that is no whole number of aligned vectors: four
+// times the load instructions for the same bytes, and a second launch for the
+// fix-up. Measured with SGD at 30,011 ids over 50K words, D = 650 fp32: walk and
+// fix-up 37.3 + 7.6 us before, 40.1 us in one launch now.
 template <typename GT, int OP, bool TAIL>
 static hipError_t launch_vec(SegArgs& a, hipStream_t st) {
   constexpr int VEC = 16 / static_cast<int>(sizeof(GT));
@@ -1191,7 +1191,13 @@ static hipError_t launch_vec(SegArgs& a, hipStream_t st) {
 template <typename GT, int OP>
 hipError_t seg_walk(SegArgs& a, hipStream_t st) {
   constexpr int VEC = 16 / static_cast<int>(sizeof(GT));
-  if (a.D < VEC) return launch_r<GT, 1, 1, OP, false>(a, st);
+  if (a.by_column) {
+    if constexpr (sizeof(GT) == 2) {
+      if (a.D > 2 * kWave) return launch_r<GT, 1, 4, OP, false>(a, st);
+      if (a.D > kWave) return launch_r<GT, 1, 2, OP, false>(a, st);
+    }
+    return launch_r<GT, 1, 1, OP, false>(a, st);
+  }
   return a.D % VEC ? launch_vec<GT, OP, true>(a, st) : launch_vec<GT, OP, false>(a, st);
 }
 

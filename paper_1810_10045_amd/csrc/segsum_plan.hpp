@@ -98,4 +98,18 @@ inline ChunkCount whole_rounds(int64_t K, int64_t u_cap, int R, bool bf16, bool 
   return c;
 }
 
+// Whether the walk reads a column per lane, not 16-byte vectors: rows shorter
+// than one, and bf16 rows of up to kMaxHalfCols columns where some vector would
+// start between two 4-byte words (grad is the rows' address, ld their stride).
+// Such a vector takes longer than eight loads of a column. One call, us, vectors
+// / columns: 300,000 ids over 221, SGD, D = 63 53.1 / 32.2, D = 255 82.3 / 47.4;
+// 36,886 over 60K, D = 31 16.4 / 14.3, D = 127 18.9 / 16.9; but D = 257 23.2 / 27.9,
+// and of even width and stride 300,000 over 221, SGD, D = 14 36.7 / 38.3.
+constexpr int kMaxHalfCols = 256;
+
+inline bool column_per_lane(uintptr_t grad, int64_t ld, int64_t D, bool bf16) {
+  if (D < (bf16 ? 8 : 4)) return true;
+  return bf16 && D <= kMaxHalfCols && (grad % 4 != 0 || ld % 2 != 0 || D % 2 != 0);
+}
+
 }  // namespace lmz

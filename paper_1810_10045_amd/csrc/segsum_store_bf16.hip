@@ -47,6 +47,8 @@ SEG_PLAIN(bf16_t, 8, 1, true)
 SEG_PLAIN(bf16_t, 8, 2, false)
 SEG_PLAIN(bf16_t, 8, 2, true)
 SEG_PLAIN(bf16_t, 1, 1, false)
+SEG_PLAIN(bf16_t, 1, 2, false)
+SEG_PLAIN(bf16_t, 1, 4, false)
 #undef SEG_PLAIN
 
 template hipError_t seg_walk<bf16_t, kOpStore>(SegArgs&, hipStream_t);

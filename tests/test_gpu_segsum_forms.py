@@ -89,6 +89,14 @@ def test_segsum_any_width(lz, gdt, D, first):
     H.assert_single_rows_exact(got, ref, o[1])
 
 
+@pytest.mark.parametrize("D,first", [(63, 0), (64, 0), (65, 1), (66, 1), (127, 0), (129, 0), (255, 0),
+                                     (256, 0), (257, 0), (250, 0), (251, 0)])
+def test_segsum_bf16_rows_between_words(lz, D, first):
+    """bf16 rows of odd width, stride or start: up to 256 columns a column per
+    lane (1, 2 and 4 for each lane), from there on vectors."""
+    test_segsum_any_width(lz, "bf16", D, first)
+
+
 @pytest.mark.parametrize("K,V,D,gdt", [(6400, 199, 1024, "f32"), (6400, 200, 512, "f32"),
                                        (6400, 201, 650, "f32"), (300_000, 200_000, 64, "f32"),
                                        (9000, 8000, 520, "bf16"), (5000, 1, 300, "f32")])

@@ -19,17 +19,25 @@ extern "C" void rounds(int64_t K, int64_t u_cap, int R, int bf16, int part_vec, 
   *n = c.n;
   *enough = c.enough;
 }
+extern "C" int by_column(uintptr_t grad, int64_t ld, int64_t D, int bf16) {
+  return lmz::column_per_lane(grad, ld, D, bf16 != 0);
+}
 """
 
 
 @pytest.fixture(scope="module")
-def plan(tmp_path_factory):
+def lib(tmp_path_factory):
     d = tmp_path_factory.mktemp("plan")
     (d / "plan.cpp").write_text(SOURCE)
     so = str(d / "plan.so")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I", CSRC, "-o", so,
                     str(d / "plan.cpp")], check=True)
-    f = ctypes.CDLL(so).rounds
+    return ctypes.CDLL(so)
+
+
+@pytest.fixture(scope="module")
+def plan(lib):
+    f = lib.rounds
     f.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int] * 6 + [ctypes.c_int64, ctypes.c_int,
                                                              ctypes.c_void_p, ctypes.c_void_p]
 
@@ -96,3 +104,14 @@ def test_the_chunk_length_stays_with_fp32_rows(plan):
 def test_an_unknown_device_keeps_the_chunks_it_needs(plan):
     assert plan(40_000, 2_000, 64, 627, blocks=0) == (627, 627)
     assert plan(40_000, 2_000, 64, 627, cus=0) == (627, 627)
+
+
+def test_bf16_rows_between_words_take_a_column_per_lane(lib):
+    f = lib.by_column
+    f.argtypes = [ctypes.c_size_t, ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
+    base = 0x7f0000001000
+    for D, ld, at, want in ((7, 7, 0, 1), (8, 8, 0, 0), (8, 8, 2, 1), (8, 9, 0, 1), (9, 10, 0, 1),
+                            (10, 10, 0, 0), (10, 10, 4, 0), (255, 255, 0, 1), (256, 256, 0, 0),
+                            (256, 257, 0, 1), (257, 257, 0, 0), (1031, 1031, 2, 0)):
+        assert f(base + at, ld, D, 1) == want, (D, ld, at)
+    assert [f(base + 4, D + 1, D, 0) for D in (1, 3, 4, 5, 255)] == [1, 1, 0, 0, 0]
