@@ -1103,8 +1103,7 @@ static void launch_one(SegArgs& a, int tiles, hipStream_t st) {
   const bool fused = VEC >= 2 && a.fused;
   const int cus = stream_cus(st);
   const int64_t room = int64_t(plain_blocks<GT, VEC, NV, R, TAIL>(fused)) * kSegWaves * cus;
-  const bool part_vec = a.D % (16 / static_cast<int>(sizeof(GT))) != 0;
-  const ChunkCount cc = whole_rounds(a.K, a.u_cap, R, sizeof(GT) == 2, part_vec, tiles, a.nchunks,
+  const ChunkCount cc = whole_rounds(a.K, a.D, a.u_cap, R, sizeof(GT) == 2, tiles, a.nchunks,
                                      a.max_chunks, room, cus);
   a.nchunks = cc.n;
   a.enough = cc.enough;

@@ -46,16 +46,17 @@ struct ChunkCount {
 //
 // Less than one round, few types: nearly every cut goes through a long segment
 // and costs a partial row, and a head's pieces are summed one after the other.
-// So only whole workgroups for each compute unit are filled up: one where
-// chunks keep kFewRows positions, or two where one and a part are needed
-// anyway (not with part_vec). us as they come / here / as with many types:
+// So only whole workgroups for each compute unit are filled up: one, or two with
+// rows of less than kNarrowBytes, of which a wave has few bytes in flight, while
+// chunks keep kFewRows positions; and two where one and a part are needed anyway
+// (not with part_vec). us as they come / here / as with many types:
 //   bf16, 30,000 ids over 98 characters, D = 1024 (950 waves) 22.7 / 22.7 /
 //     31.2; D = 352, 905,469 over 221 (1,769) 124 / 118 (2,048) / 128;
 //     D = 512, 100,000 over 500 (786) 32.9 / 29.1 (1,024) / 31.3;
 //   fp32, 60,000 over 500, D = 1024 (945) 49.2 / 49.2 / 53.7; 262,144 over 98,
 //     D = 1024 (1,025) 174 / 174 / 200; 200,000 over 98, D = 256 (782) 53 / 40
-//     (1,024) / 55; Adam, 19,200 over 98, D = 1792 (1,208) 43.0 / 39.7 (2,048)
-//     / 39.7; D = 512 (604) 17.0 / 17.0 / 17.7.
+//     (1,024) / 55, D = 128 35 (1,024) / 31 (2,048) / 37; Adam, 19,200 over 98,
+//     D = 1792 (1,208) 43.0 / 39.7 (2,048) / 39.7; D = 512 (604) 17.0 / 17.0 / 17.7.
 //
 // kEnoughWaves for each compute unit are enough with bf16 rows where far fewer
 // types turn up than there is room for, unless a chunk would exceed R: room for
@@ -66,10 +67,11 @@ struct ChunkCount {
 // 220 us, 65,536 over 800K, D = 2048 136 -> 139.
 constexpr int kFillWaves = 8, kEnoughWaves = 10;  // for each compute unit
 constexpr int kGroupWaves = 4;                    // waves of a workgroup
-constexpr int kFewTokens = 32, kFewRows = 64;
+constexpr int kFewTokens = 32, kFewRows = 64, kNarrowBytes = 1024;
 
-inline ChunkCount whole_rounds(int64_t K, int64_t u_cap, int R, bool bf16, bool part_vec, int tiles,
+inline ChunkCount whole_rounds(int64_t K, int64_t D, int64_t u_cap, int R, bool bf16, int tiles,
                                int nchunks, int max_chunks, int64_t waves_per_round, int cus) {
+  const bool part_vec = D % (bf16 ? 8 : 4) != 0;
   ChunkCount c{nchunks, nchunks};
   if (waves_per_round <= 0 || tiles <= 0 || cus <= 0) return c;
   const int64_t waves = int64_t(nchunks) * tiles;
@@ -79,10 +81,11 @@ inline ChunkCount whole_rounds(int64_t K, int64_t u_cap, int R, bool bf16, bool 
     if (last != 0 && 2 * last < waves_per_round) fill = waves - last + waves_per_round;
   } else if (K >= kFewTokens * u_cap) {
     const int64_t group = int64_t(cus) * kGroupWaves;
-    const bool two = waves > group + group / 8;
-    const int64_t want = R == kMinR || (two && part_vec) ? 0 : two ? 2 * group : group;
-    if (waves < want - want / 8 && K / (two ? kMinR : kFewRows) >= (want + tiles - 1) / tiles)
-      fill = want;
+    const bool more = waves > group + group / 8, narrow = D * (bf16 ? 2 : 4) < kNarrowBytes;
+    const int64_t want = more || narrow ? 2 * group : group;
+    const int rows = more && !narrow ? kMinR : kFewRows;
+    const bool may = R > kMinR && (narrow || !more || !part_vec);
+    if (may && waves < want - want / 8 && K / rows >= (want + tiles - 1) / tiles) fill = want;
   } else if (R >= 256) {
     fill = waves_per_round;
   } else if (R > kMinR) {

@@ -12,9 +12,9 @@ CSRC = os.path.join(ROOT, "paper_1810_10045_amd", "csrc")
 
 SOURCE = r"""
 #include "segsum_plan.hpp"
-extern "C" void rounds(int64_t K, int64_t u_cap, int R, int bf16, int part_vec, int tiles,
+extern "C" void rounds(int64_t K, int64_t D, int64_t u_cap, int R, int bf16, int tiles,
                        int nchunks, int max_chunks, int64_t room, int cus, int* n, int* enough) {
-  const lmz::ChunkCount c = lmz::whole_rounds(K, u_cap, R, bf16 != 0, part_vec != 0, tiles, nchunks,
+  const lmz::ChunkCount c = lmz::whole_rounds(K, D, u_cap, R, bf16 != 0, tiles, nchunks,
                                               max_chunks, room, cus);
   *n = c.n;
   *enough = c.enough;
@@ -38,13 +38,13 @@ def lib(tmp_path_factory):
 @pytest.fixture(scope="module")
 def plan(lib):
     f = lib.rounds
-    f.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int] * 6 + [ctypes.c_int64, ctypes.c_int,
+    f.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int] * 5 + [ctypes.c_int64, ctypes.c_int,
                                                              ctypes.c_void_p, ctypes.c_void_p]
 
-    def rounds(K, u_cap, R, need, tiles=1, bf16=0, part=0, blocks=4, cus=256, most=None):
+    def rounds(K, u_cap, R, need, tiles=1, bf16=0, D=512, blocks=4, cus=256, most=None):
         """`need` chunks; `blocks` workgroups of 4 waves fit on a compute unit."""
         n, enough = ctypes.c_int(), ctypes.c_int()
-        f(K, min(K, u_cap), R, bf16, part, tiles, need, most or 5 * K // R + 1, 4 * blocks * cus,
+        f(K, D, min(K, u_cap), R, bf16, tiles, need, most or 5 * K // R + 1, 4 * blocks * cus,
           cus, ctypes.byref(n), ctypes.byref(enough))
         return n.value, enough.value
     return rounds
@@ -52,17 +52,20 @@ def plan(lib):
 
 # Calls on 256 compute units: chunks needed (one round at most) -> chunks.
 MANY = [(40_000, 2_000, 64, 627, 2048, {}), (106_496, 800_000, 128, 1664, 2048, {}),
-        (30_011, 50_000, 32, 1876, 1876, {}), (21_386, 2_865, 32, 669, 1024, dict(part=1)),
+        (30_011, 50_000, 32, 1876, 1876, {}), (21_386, 2_865, 32, 669, 1024, dict(D=358)),
         (20_000, 5_000, 32, 629, 1250, {}), (640, 10_000, 16, 63, 63, {}),
         (100_000, 5_000, 128, 938, 2048, dict(bf16=1)),
         (524_288, 20_000, 512, 1063, 2048, dict(blocks=2)),
         (200_000, 20_000, 256, 860, 3907, dict(blocks=6))]  # the workspace's room
 FEW = [(30_000, 98, 32, 950, 950, dict(bf16=1)), (60_000, 500, 64, 945, 945, {}),
        (100_000, 500, 128, 786, 1024, dict(bf16=1)), (19_200, 98, 32, 604, 604, {}),
-       (19_200, 98, 32, 604, 1024, dict(tiles=2)), (19_200, 98, 32, 604, 604, dict(tiles=2, part=1)),
+       (19_200, 98, 32, 604, 1024, dict(tiles=2)), (19_200, 98, 32, 604, 604, dict(tiles=2, D=1791)),
        (200_000, 98, 256, 782, 1024, dict(blocks=6)), (262_144, 98, 256, 1025, 1025, {}),
        (905_469, 221, 512, 1769, 2048, dict(bf16=1)),
-       (16_000, 98, 16, 900, 900, {})]
+       (16_000, 98, 16, 900, 900, {}),
+       (300_000, 221, 512, 586, 2048, dict(bf16=1, D=14)), (300_000, 221, 512, 586, 2048, dict(D=91)),
+       (300_000, 221, 512, 586, 1024, dict(D=357)), (60_000, 221, 64, 941, 941, dict(D=64)),
+       (200_000, 98, 256, 782, 2048, dict(D=255)), (200_000, 98, 256, 782, 1024, dict(D=256))]
 
 
 @pytest.mark.parametrize("K,V,R,need,want,how", MANY + FEW)
@@ -73,17 +76,17 @@ def test_less_than_one_round(plan, K, V, R, need, want, how):
 
 
 @pytest.mark.parametrize("cus", [32, 64, 128, 224, 256])
-@pytest.mark.parametrize("part", [0, 1])
+@pytest.mark.parametrize("D", [512, 513])
 @pytest.mark.parametrize("V", [100, 4000])
-def test_waves_follow_the_compute_units_of_the_stream(plan, cus, part, V):
+def test_waves_follow_the_compute_units_of_the_stream(plan, cus, D, V):
     """Never filled above 8 waves (4 where partial rows are written a column at
     a time) for each compute unit of the stream; as many as are needed stay."""
     K, R = 100_000, 64
     for need in (16, cus, 3 * cus, 4 * cus, 5 * cus, 7 * cus, 8 * cus, 12 * cus):
-        n, enough = plan(K, V, R, need, part=part, cus=cus)
-        assert need <= n <= max(need, cus * (4 if part else 8)) and enough == n
+        n, enough = plan(K, V, R, need, D=D, cus=cus)
+        assert need <= n <= max(need, cus * (8 if D == 512 else 4)) and enough == n
         assert n in (need, 4 * cus, 8 * cus)
-        assert plan(K, V, R, need, part=part, cus=cus, bf16=1) == (n, 10 * cus)
+        assert plan(K, V, R, need, D=D, cus=cus, bf16=1) == (n, 10 * cus)
 
 
 def test_whole_rounds(plan):
