@@ -283,13 +283,15 @@ __device__ __forceinline__ int64_t out_row_of(const SegArgs& a, int s) {
   return r;
 }
 
+constexpr int kRawBufferWord3 = 0x00020000;  // buffer resources: 32-bit data format, no swizzle
+constexpr int kSc1 = 16;                     // the sc1 bit of buffer accesses: agent scope
+
 // The update instantiations: a buffer resource over row r (D fp32 values)
 // of base (the table, m or v, all of out's row stride), or over nothing for
 // r < 0: loads through an empty range read no memory and return zeros, so
 // a batch loads its table rows unconditionally.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t table_row(const SegArgs& a, float* base,
                                                             int64_t r) {
-  constexpr int kRawBufferWord3 = 0x00020000;  // 32-bit data format, no swizzle
   return __builtin_amdgcn_make_buffer_rsrc(base + (r >= 0 ? r : 0) * a.ld_out, 0,
                                            r >= 0 ? a.D * 4 : 0, kRawBufferWord3);
 }
@@ -355,20 +357,39 @@ __device__ __forceinline__ int vec_col(int col, int D) {
   return col < D ? col : D - VEC;
 }
 
-// Partial rows at agent scope: pairs of columns, or single ones where D is no
-// multiple of a vector (the rows of the workspace are D values apart).
-template <int VEC>
-__device__ __forceinline__ void store_vec_agent(float* p, const float* v) {
-  static_assert(VEC % 2 == 0, "pairs of fp32 values");
+// Partial rows at agent scope (the rows of the workspace are D values apart):
+// pairs of columns or, where D is no multiple of a vector and pairs are not
+// aligned (TAIL), 16 bytes at the alignment of a float through a buffer
+// resource over n rows. A column at a time had cost 6 of 32 us at 60,000 ids
+// over 500, D = 358, and 4 of 22 at 19,200 over 98, D = 517 (fp32). Adam's TAIL
+// kernels still load a column at a time: with vectors they need more registers
+// than three waves for each SIMD have (8,192 ids over 100K, D = 650 24.7 us, 24.1).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t part_rows(float* row, int n, int D) {
+  return __builtin_amdgcn_make_buffer_rsrc(row, 0, n * D * 4, kRawBufferWord3);
+}
+
+template <int VEC, bool TAIL>
+__device__ __forceinline__ void store_vec_agent(float* row, int D, int col, const float* v) {
+  static_assert(VEC % 4 == 0, "16-byte vectors");
+  if constexpr (TAIL) {
+    const __amdgpu_buffer_rsrc_t rs = part_rows(row, 1, D);
+    asm volatile("" : "+v"(col));  // its byte offset is made here, not kept through the walk
 #pragma unroll
-  for (int i = 0; i < VEC; i += 2)
-    st_agent(reinterpret_cast<uint64_t*>(p + i),
-             uint64_t(__float_as_uint(v[i])) | (uint64_t(__float_as_uint(v[i + 1])) << 32));
+    for (int i = 0; i < VEC; i += 4)
+      __builtin_amdgcn_raw_buffer_store_b128(
+          __builtin_bit_cast(u32x4, f32x4{v[i], v[i + 1], v[i + 2], v[i + 3]}), rs, (col + i) * 4,
+          0, kSc1);
+  } else {
+#pragma unroll
+    for (int i = 0; i < VEC; i += 2)
+      st_agent(reinterpret_cast<uint64_t*>(row + col + i),
+               uint64_t(__float_as_uint(v[i])) | (uint64_t(__float_as_uint(v[i + 1])) << 32));
+  }
 }
 
 template <int VEC, bool TAIL>
 __device__ __forceinline__ void load_vec_agent(const float* p, float* v) {
-  if constexpr (TAIL || VEC % 2 != 0) {
+  if constexpr (TAIL) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e)
       v[e] = __uint_as_float(ld_agent(reinterpret_cast<const uint32_t*>(p) + e));
@@ -379,6 +400,21 @@ __device__ __forceinline__ void load_vec_agent(const float* p, float* v) {
       v[e] = __uint_as_float(static_cast<uint32_t>(x));
       v[e + 1] = __uint_as_float(static_cast<uint32_t>(x >> 32));
     }
+  }
+}
+
+// VEC columns from col, of the row `bytes` after the resource's first.
+template <int VEC>
+__device__ __forceinline__ void load_part_vec(__amdgpu_buffer_rsrc_t rs, int bytes, int col,
+                                              float* v) {
+#pragma unroll
+  for (int i = 0; i < VEC; i += 4) {
+    const f32x4 x = __builtin_bit_cast(
+        f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (col + i) * 4, bytes, kSc1));
+    v[i] = x.x;
+    v[i + 1] = x.y;
+    v[i + 2] = x.z;
+    v[i + 3] = x.w;
   }
 }
 
@@ -457,7 +493,9 @@ __device__ __forceinline__ void fused_fix(const SegArgs& a) {
 #pragma unroll
     for (int r = 0; r < RF; ++r) {
       const int t = t0 + r * kSegWaves;
-      load_vec_agent<4, TAIL>(piece_row(a, cs, t <= P ? t : t0) + col_ld, buf[r]);
+      float* const row = piece_row(a, cs, t <= P ? t : t0);
+      if constexpr (TAIL && OP != kOpAdam) load_part_vec<4>(part_rows(row, 1, D), 0, col_ld, buf[r]);
+      else load_vec_agent<4, TAIL>(row + col_ld, buf[r]);
     }
 #pragma unroll
     for (int r = 0; r < RF; ++r)
@@ -696,13 +734,7 @@ __global__ __launch_bounds__(kSegThreads) void k_segsum(SegArgs a) {
   // Vector v's columns of a partial row.
   auto put_part = [&](float* row, int v) {
     if constexpr (FUSED) {
-      if constexpr (TAIL) {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e)
-          st_agent(reinterpret_cast<uint32_t*>(row + col_ld[v] + e), __float_as_uint(acc[v][e]));
-      } else {
-        store_vec_agent<VEC>(row + col_ld[v], acc[v]);
-      }
+      store_vec_agent<VEC, TAIL>(row, D, col_ld[v], acc[v]);
     } else {
       store_vec<VEC>(row + col_ld[v], acc[v]);
     }
@@ -875,27 +907,57 @@ __global__ __launch_bounds__(kSegThreads) void k_segsum(SegArgs a) {
       if (lane == 0)
         n = word_count(word_add(AgentWords{}, first_word + size_t(cs) * a.tiles, 1));
       if (first_lane(n) != P + 1) return;
+      asm volatile("" ::: "memory");  // no piece is read before its count
       // The last one: every piece is there.
       constexpr int RP = NV * VEC >= 16 ? 4 : 8;  // pieces in flight
 #pragma unroll
       for (int v = 0; v < NV; ++v)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) acc[v][e] = 0.f;
-      for (int t0 = 0; t0 <= P; t0 += RP) {
-        float buf[RP][NV][VEC];
+      if constexpr (TAIL && OP != kOpAdam) {
+        // Two resources for all of them, piece 0 and the others.
+        float p0[NV][VEC];
+        const __amdgpu_buffer_rsrc_t first = part_rows(piece_row(a, cs, 0), 1, D);
+        const __amdgpu_buffer_rsrc_t rest = part_rows(piece_row(a, cs, 1), P, D);
 #pragma unroll
-        for (int r = 0; r < RP; ++r)
+        for (int v = 0; v < NV; ++v) load_part_vec<VEC>(first, 0, col_ld[v], p0[v]);
+        for (int t0 = 1; t0 <= P; t0 += RP) {
+          float buf[RP][NV][VEC];
 #pragma unroll
-          for (int v = 0; v < NV; ++v)
-            load_vec_agent<VEC, TAIL>(piece_row(a, cs, t0 + r <= P ? t0 + r : 0) + col_ld[v],
-                                      buf[r][v]);
+          for (int r = 0; r < RP; ++r)
 #pragma unroll
-        for (int r = 0; r < RP; ++r)
-          if (t0 + r <= P)
+            for (int v = 0; v < NV; ++v)
+              load_part_vec<VEC>(rest, (t0 + r <= P ? t0 + r - 1 : 0) * D * 4, col_ld[v], buf[r][v]);
+          if (t0 == 1)
 #pragma unroll
             for (int v = 0; v < NV; ++v)
 #pragma unroll
-              for (int e = 0; e < VEC; ++e) acc[v][e] += buf[r][v][e];
+              for (int e = 0; e < VEC; ++e) acc[v][e] += p0[v][e];
+#pragma unroll
+          for (int r = 0; r < RP; ++r)
+            if (t0 + r <= P)
+#pragma unroll
+              for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) acc[v][e] += buf[r][v][e];
+        }
+      } else {
+        for (int t0 = 0; t0 <= P; t0 += RP) {
+          float buf[RP][NV][VEC];
+#pragma unroll
+          for (int r = 0; r < RP; ++r)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+              load_vec_agent<VEC, TAIL>(piece_row(a, cs, t0 + r <= P ? t0 + r : 0) + col_ld[v],
+                                  buf[r][v]);
+#pragma unroll
+          for (int r = 0; r < RP; ++r)
+            if (t0 + r <= P)
+#pragma unroll
+              for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) acc[v][e] += buf[r][v][e];
+        }
       }
       if (s >= a.u_cap) return;
       const int64_t orow = out_row_of(a, s);

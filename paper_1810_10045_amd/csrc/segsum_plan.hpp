@@ -40,9 +40,11 @@ struct ChunkCount {
 //   77 (1,664) -> 73. Close to kFillWaves it loses: 30,011 over 50K, D = 650
 //   38.3 (1,876) -> 40.5. So does it with chunks of 10 rows: 20,000 over 98,
 //   D = 200 17.2 us (2,048), 13.6 (1,280).
-//   Rows that are no whole number of vectors (part_vec) write their partial
-//   rows a column at a time: half as many waves. 21,386 over 2,865, D = 358:
-//   22.2 us (2,048), 17.7 (1,024), 18.9 (669 as they come).
+//   Rows that are no whole number of vectors (part_vec): half as many waves,
+//   which is better with short chunks (R = 32, 64) and not with longer ones. us
+//   with kFillWaves / half: 21,386 over 2,865, D = 358 15.3 / 14.3; 40,000 over
+//   2,000, D = 301 21.6 / 18.8; but R = 128, 106,496 over 800K, D = 510 63.4 /
+//   68.4, and bf16, 100,000 over 5,000, D = 518 33.7 / 39.6.
 //
 // Less than one round, few types: nearly every cut goes through a long segment
 // and costs a partial row, and a head's pieces are summed one after the other.

@@ -176,3 +176,33 @@ def test_sums_where_chunks_are_made_to_fill_the_device(lz, K, V, D, gdt):
     lz.check(r.dev_err)
     U = int(r.num_unique.item())
     assert torch.equal(out[:U].double(), want[r.uniq[:U].long()].double())
+
+
+@pytest.mark.parametrize("length", [1, 9, 40, 300, 1500])
+@pytest.mark.parametrize("D,gdt", [(5, "f32"), (517, "f32"), (1022, "f32"), (9, "bf16"), (1101, "bf16")])
+def test_pieces_of_rows_that_are_no_whole_vectors(lz, length, D, gdt):
+    """Cut segments of `length` tokens whose partial rows start at the alignment
+    of a float: a few pieces, the sixteenth, and heads; written, and applied by
+    SGD and Adam. Rows of small whole numbers, whose sums are exact in fp32."""
+    K, V = 6000, 9000
+    print(f"pieces of {length} D={D} {gdt}", flush=True)
+    base = np.repeat(np.arange((K + length - 1) // length) + 3, length)[:K].astype(np.int32)
+    rng = np.random.Generator(np.random.PCG64(900 + length + D))
+    ids = torch.from_numpy(rng.permutation(base)).to(DEV)
+    grad = torch.from_numpy(rng.integers(-8, 9, (K, D))).to(DEV)
+    want = torch.zeros((V, D), dtype=torch.int64, device=DEV).index_add_(0, ids.long(), grad).float()
+    grad = grad.to(torch.bfloat16 if gdt == "bf16" else torch.float32)
+    r = lz.unique(ids, V)
+    seg = (grad, r.perm, r.inverse, r.offsets, r.num_unique)
+    U = int(r.num_unique.item())
+    ws = lz.Workspace(DEV)
+    for _ in range(2):
+        out = lz.segsum(*seg, dev_err=r.dev_err, ws=ws)
+        assert torch.equal(out[:U], want[r.uniq[:U].long()])
+    t = torch.zeros((V, D), device=DEV)
+    lz.segsum_sgd(*seg, r.uniq, t, -1.0, dev_err=r.dev_err, ws=ws)
+    assert torch.equal(t, want)
+    p, m, v = (torch.zeros((V, D), device=DEV) for _ in range(3))
+    lz.segsum_adam(*seg, r.uniq, p, m, v, lr=0.0, beta1=0.0, step=1, dev_err=r.dev_err, ws=ws)
+    assert torch.equal(m, want)
+    lz.check(r.dev_err)
