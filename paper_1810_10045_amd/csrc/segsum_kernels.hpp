@@ -78,18 +78,12 @@ namespace lmz {
 #ifndef LMZ_SEG_RF2_LONG
 #define LMZ_SEG_RF2_LONG 16
 #endif
-#ifndef LMZ_SEG_SGD_ENDS4
-#define LMZ_SEG_SGD_ENDS4 2          // early updates: segment ends (table rows) per gather batch
-#endif                               // with 4, 2 and 1 vectors per lane
 #ifndef LMZ_SEG_SGD_ENDS2
-#define LMZ_SEG_SGD_ENDS2 4
-#endif
+#define LMZ_SEG_SGD_ENDS2 4          // early updates: segment ends (table rows) per gather batch
+#endif                               // with 2 and 1 vectors per lane
 #ifndef LMZ_SEG_SGD_ENDS1
 #define LMZ_SEG_SGD_ENDS1 6
 #endif
-#ifndef LMZ_SEG_SGD_RF4
-#define LMZ_SEG_SGD_RF4 3            // lm_segsum_sgd: rows per batch with 4 vectors per lane,
-#endif                               // chunks below LMZ_SEG_LONG_R (others as lm_segsum)
 #ifndef LMZ_SEG_ADAM_RF4
 #define LMZ_SEG_ADAM_RF4 4           // lm_segsum_adam: most rows per batch with 4 vectors per lane
 #endif
@@ -426,7 +420,7 @@ __device__ __forceinline__ float* piece_row(const SegArgs& a, int cs, int t) {
 
 template <int NV>
 constexpr int ends_for() {
-  return NV >= 4 ? LMZ_SEG_SGD_ENDS4 : NV == 2 ? LMZ_SEG_SGD_ENDS2 : LMZ_SEG_SGD_ENDS1;
+  return NV == 2 ? LMZ_SEG_SGD_ENDS2 : LMZ_SEG_SGD_ENDS1;
 }
 
 // Every lane of the wave calls this; the lanes with need wait until chunk x's
@@ -1121,15 +1115,6 @@ constexpr int rf_for() {
                  : (R >= LMZ_SEG_LONG_R ? LMZ_SEG_RF2_LONG : LMZ_SEG_RF2);
 }
 
-// lm_segsum_sgd's rows per batch, whose table rows take registers too.
-// Measured at 65,536 ids over 800K words, D = 1024 (at most two ends per
-// batch): 3 rows 98.4 us per call, 2 rows 99-101, 4 rows (lm_segsum's) 102,
-// 5 rows 106; one end per batch 118 us with 4 rows, 111 with 3.
-template <int NV, int R>
-constexpr int rf_sgd_for() {
-  return NV >= 4 && R < LMZ_SEG_LONG_R ? LMZ_SEG_SGD_RF4 : rf_for<NV, R>();
-}
-
 // lm_segsum_adam's rows per batch: as lm_segsum's, but for its three table
 // rows at most 4 rows of 4 vectors, or 8 of fewer.
 template <int NV, int R>
@@ -1147,8 +1132,7 @@ int plain_blocks(bool fused);
 template <typename GT, int VEC, int NV, int R, int OP, bool TAIL, bool EARLY>
 static void launch_one(SegArgs& a, int tiles, hipStream_t st) {
   constexpr int T = t_for<R>();
-  constexpr int RF = EARLY ? rf_sgd_for<NV, R>()
-                     : OP == kOpAdam ? rf_adam_for<NV, R>() : rf_for<NV, R>();
+  constexpr int RF = OP == kOpAdam ? rf_adam_for<NV, R>() : rf_for<NV, R>();
   constexpr int CT = NV * kWave * VEC;
   a.tiles = tiles;
   a.tile_cols = CT;
@@ -1185,30 +1169,36 @@ static void launch_one(SegArgs& a, int tiles, hipStream_t st) {
 
 // Whether an update loads the table rows of a batch's segment ends with the
 // batch's gradient rows (early). An end then costs no round trip of its own,
-// but a batch closes at its second end and has room for fewer gradient rows.
-// Otherwise (late) the walk keeps lm_segsum's batches, waits for the table row
-// at every end, and needs fewer registers (more waves hide the waits).
+// but a batch closes at its last end and takes more registers. Otherwise (late)
+// the walk keeps lm_segsum's batches and waits for the table row at every end.
 // Measured, early / late, us per call:
-//   SGD fp32, D = 1024: 65,536 ids over 800K words 86.9 / 94.0, 200,000 over
-//     100K 288 / 315, over 12,500 (K / V = 16) 208 / 216, over 6,250 (32) 203 /
-//     195, over 781 176 / 151; D = 512: 600,000 over 300K (chunks of 512)
-//     469 / 412;
+//   SGD fp32, up to 512 columns: 106,496 ids over 800K words, D = 512 72.7 /
+//     75.4, 30,011 over 50K, D = 300 18.1 / 19.0, 40,000 over 2,000 21.6 / 20.3;
+//     600,000 over 300K (chunks of 512) 469 / 412;
+//   wider (4 vectors per lane; early 3 rows and 2 ends per batch): D = 1024,
+//     65,536 over 800K 85.4 / 84.6, 200,000 over 100K 220 / 207, over 12,500 193 /
+//     181, 262,144 over 2M 383 / 366, 8,192 over 100K 16.9 / 18.1; D = 1792, 19,200
+//     over 15,437 53.1 / 51.8; D = 2048, 65,536 over 800K 165 / 162. With Unique
+//     beside it on another stream, 65,536 over 800K, D = 1024: a step 110.9 / 102.5
+//     (early, four workgroups take every register of a compute unit, and
+//     Unique's kernels wait for them);
 //   SGD bf16, D = 1024: 100,000 ids over 100K words 93.4 / 84.8;
-//   Adam (one end, 2 rows per batch early), the same tables: 262,144 ids over
-//     2M words 954 / 909, 65,536 over 800K 226 / 210, 200,000 over 400K 646 /
-//     494, D = 1792: 19,200 over 98 67 / 39. Late with 2 or 3 rows per batch,
+//   Adam (one end, 2 rows per batch early), D = 1024: 262,144 ids over 2M words
+//     954 / 909, 65,536 over 800K 226 / 210, 200,000 over 400K 646 / 494,
+//     D = 1792: 19,200 over 98 67 / 39. Late with 2 or 3 rows per batch,
 //     or loading the three rows' vectors one or two at a time, measured within
 //     2% of 4 rows and all vectors at the large sizes and 1-10% slower at
 //     19,200 ids.
-// So only SGD with fp32 rows, chunks below 512 rows and no more than 32
-// tokens per type it may find (there are at most min(K, rows_cap)) is early.
-template <typename GT, int OP, int R>
+// So only SGD with fp32 rows of up to 512 columns, chunks below 512 rows and no
+// more than 32 tokens per type it may find (there are at most min(K, rows_cap))
+// is early.
+template <typename GT, int NV, int OP, int R>
 constexpr bool may_be_early() {
-  return OP == kOpSgd && sizeof(GT) == 4 && R < LMZ_SEG_LONG_R;
+  return OP == kOpSgd && sizeof(GT) == 4 && NV <= 2 && R < LMZ_SEG_LONG_R;
 }
 template <typename GT, int VEC, int NV, int R, int OP, bool TAIL>
 static void launch_when(SegArgs& a, int tiles, hipStream_t st) {
-  if constexpr (may_be_early<GT, OP, R>()) {
+  if constexpr (may_be_early<GT, NV, OP, R>()) {
     if (a.K < kFewTokens * a.u_cap) {
       launch_one<GT, VEC, NV, R, OP, TAIL, true>(a, tiles, st);
       return;
