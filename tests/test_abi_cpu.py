@@ -181,3 +181,16 @@ def test_argument_errors_return_before_any_launch(lib):
     assert lib.lm_map_ids(_v(), _v(), 4, _v(), _v(), 4, 3, _v(), _v(), None) == 5
     assert lib.lm_map_ids(None, _v(), 4, _v(), _v(), 4, 0, _v(), _v(), None) == 1
     assert lib.lm_map_ids(_v(), _v(), 4, _v(), _v(), -1, 0, _v(), _v(), None) == 1
+
+
+def test_stream_handle_without_the_private_call(monkeypatch):
+    """Where torch has no call that returns the current stream's handle alone,
+    the binding takes the handle from the public one."""
+    from types import SimpleNamespace
+
+    import torch
+    from paper_1810_10045_amd import lmzipf as lz
+    monkeypatch.setattr(lz, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=0x7f01))
+    assert lz._stream() == 0x7f01
+    assert lz._stream(SimpleNamespace(cuda_stream=0x7f02)) == 0x7f02
