@@ -4,6 +4,7 @@
 #include <cstdlib>
 
 #include "segsum_args.hpp"
+#include "segsum_words.hpp"
 
 namespace lmz {
 
@@ -18,7 +19,7 @@ namespace lmz {
 #define LMZ_SEG_WRITE_X2_BF16 4      // bf16 rows: the same ratio, times 2
 #endif
 #ifndef LMZ_SEG_FUSED
-#define LMZ_SEG_FUSED 1              // fix-up workgroups in the walk's launch (one column tile)
+#define LMZ_SEG_FUSED 1              // the fix-up in the walk's launch
 #endif
 #ifndef LMZ_SEG_FUSED_MAX_D
 #define LMZ_SEG_FUSED_MAX_D 4096     // widest rows walked and fixed up in one launch
@@ -204,9 +205,9 @@ int segsum_run(const void* grad, int gtype, int64_t K, int64_t D, int64_t ld_gra
     }
   }
   if (a.fused) {
-    static std::atomic<uint64_t> calls{0x3779b97f4a7ull};  // any start
+    static std::atomic<uint64_t> calls{0x9e3779b97f4a7cull};  // any start
     a.flags = reinterpret_cast<uint64_t*>(w + L.flags);
-    a.tag = calls.fetch_add(1, std::memory_order_relaxed) & ((uint64_t(1) << 44) - 1);
+    a.tag = calls.fetch_add(1, std::memory_order_relaxed) & kTagMask;
     const bool fail = g_force_wait_failure.load(std::memory_order_relaxed);
     a.wait_tag = fail ? ~a.tag : a.tag;
     a.spin_limit = fail ? g_forced_spin_limit.load(std::memory_order_relaxed) : kSpinLimit;

@@ -254,6 +254,7 @@ __device__ __forceinline__ void chunk_bounds(const int (&s_win)[N + 1], int lo, 
 #define LMZ_SEG_FUSED_SLEEP 8        // s_sleep argument (x 64 cycles) between flag polls
 #endif
 constexpr int kHeadPieces = 16;  // further pieces from which a segment is a head
+static_assert(kHeadPieces <= kCountMask, "a word counts a segment's pieces");
 // The memory operations of the words (segsum_words.hpp).
 struct AgentWords {
   __device__ __forceinline__ void exchange_if(uint64_t* w, uint64_t seen, uint64_t x) const {

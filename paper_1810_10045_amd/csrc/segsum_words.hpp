@@ -6,7 +6,8 @@
 //
 // A word: a tag that is new for every call, a flag (the chunk's own piece of a
 // head is there) and a count (pieces that are there of the segment that starts
-// in the chunk). What an earlier call or other data left carries another tag.
+// in the chunk, at most 16). What an earlier call left carries another tag, and
+// of other data one word in 2^56 carries this call's.
 //
 // A wave claims every word that it will add to, before its walk: it loads the
 // word and, where the tag is another's, tries once to exchange what it loaded
@@ -23,7 +24,7 @@
 
 namespace lmz {
 
-constexpr int kTagShift = 20;
+constexpr int kTagShift = 8;
 constexpr uint64_t kTagMask = (uint64_t(1) << (64 - kTagShift)) - 1;
 constexpr uint64_t kPieceFlag = uint64_t(1) << (kTagShift - 1);
 constexpr uint64_t kCountMask = kPieceFlag - 1;

@@ -198,6 +198,17 @@ def model(tmp_path_factory):
     return exe
 
 
+def test_a_word_is_wide_enough(tmp_path):
+    """The tag takes all but a byte of a word, the count 16 pieces and a flag."""
+    (tmp_path / "w.cpp").write_text('''#include "segsum_words.hpp"
+using namespace lmz;
+static_assert(kTagShift <= 8 && kCountMask >= 16 && (kPieceFlag & kCountMask) == 0);
+static_assert(word_is((kTagMask << kTagShift) | kPieceFlag | kCountMask, kTagMask));
+static_assert(word_count((kTagMask << kTagShift) | kPieceFlag | 16) == 16);
+''')
+    subprocess.run(["g++", "-std=c++17", "-fsyntax-only", "-I", CSRC, str(tmp_path / "w.cpp")], check=True)
+
+
 def test_every_interleaving_finishes_each_segment_once(model):
     r = subprocess.run([model, "0"], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout
