@@ -173,14 +173,17 @@ int lm_unique_noalloc(const void* ids, int32_t idtype, int64_t K, int64_t V,
  * ws         device workspace of lm_segsum_workspace_bytes(K, D) bytes,
  *            256-byte aligned; no initial contents are required.
  *
- * With D <= 4096 and rows of at least 16 bytes, the segments that span the
- * walk's chunks are summed in the same launch, by the wave that finishes their
- * last piece or, the longest ones, by workgroups that wait for the pieces
- * (bounded waits; LM_DEVERR_SPIN if one gave up, which a correct call never
- * does). Pieces are announced in words tagged with a per-call value from a
- * process-wide counter. Otherwise, always while `stream` is being captured
- * into a graph (a replay would repeat the tag), and while
- * lm_segsum_set_two_launches is on,
+ * The segments that span the walk's chunks are summed in the same launch, by
+ * the wave that finishes their last piece or, the longest ones, by workgroups
+ * that wait for the pieces (bounded waits; LM_DEVERR_SPIN if one gave up, which a
+ * correct call never does). Pieces are announced in words tagged with a per-call
+ * value from a process-wide counter. In these cases
+ *   - D > 4096, or rows of less than 16 bytes;
+ *   - D > 1024 and D mod 1024 columns, the last column tile, are less than 16
+ *     bytes (1 to 3 fp32 columns, 1 to 7 bf16);
+ *   - bf16 rows of D <= 256 with D or ld_grad odd or grad no multiple of 4 bytes;
+ *   - `stream` is being captured into a graph (a replay would repeat the tag);
+ *   - lm_segsum_set_two_launches is on;
  * they are summed by a second launch.
  * ------------------------------------------------------------------------ */
 size_t lm_segsum_workspace_bytes(int64_t K, int64_t D);
