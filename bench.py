@@ -50,8 +50,8 @@ HBM_PEAK_GBPS = 8000.0
 METRIC = "tokens/s through Unique+Seg-Sum+Fill-Values; achieved HBM GB/s vs peak"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "segsum_traffic_{workload}.md")
 SEGSUM_SRCS = [os.path.join(ROOT, "paper_1810_10045_amd", "csrc", f)
-               for f in ("segsum.hip", "segsum_args.hpp", "segsum_kernels.hpp", "segsum_plan.hpp",
-                         "segsum_words.hpp", "common.hpp")]
+               for f in ("segsum.hip", "segsum_args.hpp", "segsum_kernels.hpp", "segsum_plain.hpp",
+                         "segsum_plan.hpp", "segsum_words.hpp", "common.hpp")]
 COPY_BYTES = 1 << 30  # the plain copy that scales the HBM byte counters
 SEGSUM_KERNELS = "lm_segsum (k_segsum: walk and fix-up workgroups in one launch)"
 
