@@ -357,8 +357,9 @@ __device__ __forceinline__ int vec_col(int col, int D) {
 // aligned (TAIL), 16 bytes at the alignment of a float through a buffer
 // resource over n rows. A column at a time had cost 6 of 32 us at 60,000 ids
 // over 500, D = 358, and 4 of 22 at 19,200 over 98, D = 517 (fp32). Adam's TAIL
-// kernels still load a column at a time: with vectors they need more registers
-// than three waves for each SIMD have (8,192 ids over 100K, D = 650 24.7 us, 24.1).
+// kernels still load a column at a time, which measured faster where there are
+// few pieces (640 ids over 10K, D = 517 17.6 us, 19.0; 65,536 over 800K, D = 513
+// 90.4, 94.2).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t part_rows(float* row, int n, int D) {
   return __builtin_amdgcn_make_buffer_rsrc(row, 0, n * D * 4, kRawBufferWord3);
 }
@@ -484,6 +485,7 @@ __device__ __forceinline__ void fused_fix(const SegArgs& a) {
   for (int t0 = wave; t0 <= P; t0 += kSegWaves * RF) {
     const int tl = t0 + (lane < RF ? lane : 0) * kSegWaves;  // lane r: piece t0 + r * W
     wait_piece(a, cs + (tl <= P ? tl : 0), ct, lane < RF && tl <= P);
+    asm volatile("" ::: "memory");  // no piece is read before its flag
     float buf[RF][4];
 #pragma unroll
     for (int r = 0; r < RF; ++r) {
@@ -516,9 +518,16 @@ __device__ __forceinline__ void fused_fix(const SegArgs& a) {
   }
 }
 
+// Adam in one launch with 4 vectors per lane runs two workgroups on a compute
+// unit, also where its registers allow three (168 of them at R = 16 and 32):
+// then the walk's 512 workgroups spread evenly and the fix-up's start after
+// them. us, three / two: 19,200 ids over 98, D = 1792 39.4 / 37.8, over 15,437
+// 82.2 / 76.7; 30,011 over 50K, D = 650 50.7 / 47.9; 65,536 over 800K, D = 1024
+// 176.6 / 176.1.
 template <typename GT, int VEC, int NV, int RF, int R, int T, bool FUSED, int OP,
           bool TAIL, bool EARLY>
-__global__ __launch_bounds__(kSegThreads) void k_segsum(SegArgs a) {
+__global__ __launch_bounds__(kSegThreads)
+__attribute__((amdgpu_waves_per_eu(1, FUSED && OP == kOpAdam && NV >= 4 ? 2 : 8))) void k_segsum(SegArgs a) {
   if constexpr (FUSED) {
     if (static_cast<int>(blockIdx.x) >= a.main_blocks) {
       fused_fix<OP, TAIL>(a);
