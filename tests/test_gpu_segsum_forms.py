@@ -206,3 +206,29 @@ def test_pieces_of_rows_that_are_no_whole_vectors(lz, length, D, gdt):
     lz.segsum_adam(*seg, r.uniq, p, m, v, lr=0.0, beta1=0.0, step=1, dev_err=r.dev_err, ws=ws)
     assert torch.equal(m, want)
     lz.check(r.dev_err)
+
+
+@pytest.mark.parametrize("D,gdt", [(512, "f32"), (517, "f32"), (1100, "bf16")])
+def test_words_that_the_call_before_left(lz, D, gdt):
+    """Calls on one workspace, in turn over lists whose heads and cut segments of
+    a few pieces end and start in the same chunks: every chunk's word holds a
+    flag, a count or both from the call before. Rows of small whole numbers."""
+    K, V = 6000, 500
+    print(f"words of the call before D={D} {gdt}", flush=True)
+    rng = np.random.Generator(np.random.PCG64(1000 + D))
+    ws, calls = lz.Workspace(DEV), []
+    for lengths in ((300, 40), (40, 300, 24), (24, 700)):
+        n = np.resize(lengths, K)
+        base = np.repeat(np.arange(K), n)[:K].astype(np.int32)
+        ids = torch.from_numpy(rng.permutation(base)).to(DEV)
+        grad = torch.from_numpy(rng.integers(-8, 9, (K, D))).to(DEV)
+        want = torch.zeros((V, D), dtype=torch.int64, device=DEV).index_add_(0, ids.long(), grad)
+        grad = grad.to(torch.bfloat16 if gdt == "bf16" else torch.float32)
+        r = lz.unique(ids, V)
+        calls.append((r, (grad, r.perm, r.inverse, r.offsets, r.num_unique), want.float()))
+    outs = [(r, lz.segsum(*seg, dev_err=r.dev_err, ws=ws), want)
+            for _ in range(4) for r, seg, want in calls]
+    for r, out, want in outs:
+        U = int(r.num_unique.item())
+        assert torch.equal(out[:U], want[r.uniq[:U].long()])
+        lz.check(r.dev_err)
